@@ -154,9 +154,8 @@ static void free_plan(blast_plan *p) {
     f(p->d_ell);
     f(p->d_elli);
     f(p->scratch);
-    f(p->d_fd);
+    f(p->d_lima);
     f(p->d_fds);
-    f(p->limb_ws);
     for (hipEvent_t e : p->prof_events) (void)hipEventDestroy(e);
     delete p;
 }
@@ -325,7 +324,17 @@ static blast_status plan_create_impl(const blast_plan_desc *d, int32_t device, B
             std::vector<double> fd;
             std::vector<int> fds;
             derivative_stencils(p->chi, fd, fds);
-            e = up((void **)&p->d_fd, fd.data(), fd.size() * sizeof(double));
+            // A = sqrt(chi) (chi^2/2 Kt'' + chi^3/6 Kt''') with Kt = K / sqrt(chi), as weights of K
+            std::vector<double> lima((size_t)p->n_chi * 5);
+            for (int a = 0; a < p->n_chi; ++a)
+                for (int q = 0; q < 5; ++q) {
+                    const double x = p->chi[a];
+                    lima[(size_t)a * 5 + q] = std::sqrt(x) *
+                                              (0.5 * x * x * fd[((size_t)a * 2 + 0) * 5 + q] +
+                                               x * x * x / 6.0 * fd[((size_t)a * 2 + 1) * 5 + q]) /
+                                              std::sqrt(p->chi[fds[a] + q]);
+                }
+            e = up((void **)&p->d_lima, lima.data(), lima.size() * sizeof(double));
             if (e == hipSuccess) e = up((void **)&p->d_fds, fds.data(), fds.size() * sizeof(int));
         }
         if (e != hipSuccess) {

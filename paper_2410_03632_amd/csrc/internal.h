@@ -112,12 +112,10 @@ struct blast_plan {
     // plan-owned scratch for calls without a caller workspace
     void *scratch = nullptr;
     size_t scratch_bytes = 0;
-    // Limber path: 5-node stencils for the second and third derivative at each chi node
-    // (weights [n_chi][2][5], first node [n_chi]; absent when n_chi < 5) and its own scratch
-    double *d_fd = nullptr;
+    // Limber path: A(chi_a) = sum_q lima[a][q] K(chi_{fds[a] + q}), the extended approximation's
+    // derivative term from the 5-node stencils (absent when n_chi < 5)
+    double *d_lima = nullptr;
     int *d_fds = nullptr;
-    void *limb_ws = nullptr;
-    size_t limb_ws_bytes = 0;
     std::mutex mu;
 };
 
