@@ -384,9 +384,10 @@ blast_status blast_server_destroy(blast_server *srv);
 
 /* While enabled, blast_cl_forward records HIP events on the call's stream around
  * four intervals: 0 projection, 1 contraction, 2 R-quadrature, 3 chi-quadrature and
- * pair assembly.  On the mixed-precision paths without w_save, where the contraction
- * and the R-quadrature run fused, interval 1 holds the R-quadrature weight table and
- * interval 2 the fused kernel.  The events cost a few microseconds per call. */
+ * pair assembly.  Where the contraction and the R-quadrature run fused (the
+ * mixed-precision paths without w_save, FP64 and FP32 below 32 cosmologies, FP64 from
+ * there on with at most 16 bins), interval 1 holds the R-quadrature weight table, if the
+ * call makes one, and interval 2 the fused kernel.  The events cost a few microseconds per call. */
 blast_status blast_plan_profile(blast_plan *plan, int32_t enable);
 
 /* ------------------------------------------------------------------------ */

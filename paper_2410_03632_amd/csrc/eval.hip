@@ -2315,6 +2315,154 @@ __global__ __launch_bounds__(256) void quad_c_mfma_kernel(const YT *__restrict__
     }
 }
 
+// quad_c_mfma_kernel for calls whose 16-row work-groups would leave the chip idle: four rows per work-group,
+// one per wave, with the first loads of Y ahead of the K table and whole lines of K_chi read for it.  Y may
+// be the sum of nsplit ranges, ysplit values apart.  The sums over the chi nodes run in the same order.
+template <typename YT, int NBT>
+__global__ __launch_bounds__(256, NBT == 1 ? (sizeof(YT) == 8 ? 3 : 4) : 2) void quad_c_few_kernel(const YT *__restrict__ Y, int nsplit, size_t ysplit,
+                                                          const double *__restrict__ Kchi,
+                                                          const double *__restrict__ wchi,
+                                                          const double *__restrict__ chi,
+                                                          const double *__restrict__ pref, int n_chi, int rows_pad,
+                                                          int n_ell, Slots slot_type, int ng, int ns, uint32_t types,
+                                                          int npairs, EllSel sel, double *__restrict__ C) {
+    constexpr int NBP = 16 * NBT, CR = 4;
+    extern __shared__ __align__(16) double smem_c[];
+    const int nbins = ng + ns;
+    const int nc4 = (n_chi + 3) & ~3;
+    // [nc4][NBP], bin b of node a at b ^ (a & 15): the 16 lanes of a K-step read the 16 bins of one chi
+    // node, and the lanes that fill the table write one bin of 16 nodes, from and to 16 places of a row
+    double *Kt = smem_c;
+    double *Zs = smem_c + (size_t)NBP * nc4;       // [4 waves][NBP][NBP]
+    const int nblk = (sel.n_out + CR - 1) / CR;
+    const int slot = blockIdx.x / nblk, io0 = (blockIdx.x % nblk) * CR;
+    const int beta = blockIdx.y;
+    const int t = slot_type.s[slot];
+    if (!(t & types)) return;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int lr = lane & 15, lk = lane >> 4;
+    const int nsteps = nc4 / 4;
+    // blocks of KB K-steps whose raw loads go out together (clamped addresses, values masked past n_chi);
+    // the first block ahead of the table
+    constexpr int KB = sizeof(YT) == 8 ? 16 / NBT : 16;
+    const int io = io0 + wv;  // (uniform over the wave)
+    const int row = slot * n_ell + sel.idx[min(io, sel.n_out - 1)];
+    const YT *yr = Y + ((size_t)beta * rows_pad + row) * n_chi * NBP;
+    YT bv[KB][NBT];
+    auto load_block = [&](int s0) {
+#pragma unroll
+        for (int u = 0; u < KB; ++u) {
+            const int ac = min(4 * (s0 + u) + lk, n_chi - 1);
+#pragma unroll
+            for (int i = 0; i < NBT; ++i) bv[u][i] = yr[(uint32_t)(ac * NBP + 16 * i + lr)];
+        }
+        for (int sp = 1; sp < nsplit; ++sp) {
+            const YT *ys = yr + (size_t)sp * ysplit;
+#pragma unroll
+            for (int u = 0; u < KB; ++u) {
+                const int ac = min(4 * (s0 + u) + lk, n_chi - 1);
+#pragma unroll
+                for (int i = 0; i < NBT; ++i) bv[u][i] += ys[(uint32_t)(ac * NBP + 16 * i + lr)];
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    load_block(0);
+    // table: wave wv takes bins wv, wv + 4, ..., a lane consecutive chi nodes (whole lines of K_chi)
+    for (int a0 = 0; a0 < nc4; a0 += 128) {
+        double kv[2][NBP / 4], wc[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int ac = min(a0 + 64 * h + lane, n_chi - 1);
+            wc[h] = wchi[ac] * chi[ac];
+#pragma unroll
+            for (int q = 0; q < NBP / 4; ++q)
+                kv[h][q] = Kchi[((size_t)beta * nbins + min(4 * q + wv, nbins - 1)) * n_chi + ac];
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int a = a0 + 64 * h + lane;
+#pragma unroll
+            for (int q = 0; q < NBP / 4; ++q) {
+                const int bin = 4 * q + wv;
+                if (a < nc4) Kt[a * NBP + (bin ^ (a & 15))] = (bin < nbins && a < n_chi) ? wc[h] * kv[h][q] : 0.0;
+            }
+        }
+    }
+    __syncthreads();
+    int off, ntp;
+    if (t == BLAST_GG) {
+        off = 0;
+        ntp = ng * (ng + 1) / 2;
+    } else if (t == BLAST_GS) {
+        off = (types & BLAST_GG) ? ng * (ng + 1) / 2 : 0;
+        ntp = ng * ns;
+    } else {
+        off = ((types & BLAST_GG) ? ng * (ng + 1) / 2 : 0) + ((types & BLAST_GS) ? ng * ns : 0);
+        ntp = ns * (ns + 1) / 2;
+    }
+    double *Z = Zs + (size_t)wv * NBP * NBP;
+    const auto pair_of = [&](int q, int &i, int &j) {
+        if (t == BLAST_GS) {
+            i = q / ns;
+            j = ng + q % ns;
+            return;
+        }
+        const int n = t == BLAST_GG ? ng : ns, base = t == BLAST_GG ? 0 : ng;
+        int r = 0;
+        while (q >= n - r) {
+            q -= n - r;
+            ++r;
+        }
+        i = base + r;
+        j = base + r + q;
+    };
+    double *Ct = C + ((size_t)beta * npairs + off) * sel.n_out;
+    if (io < sel.n_out) {
+        d4 acc[NBT][NBT];
+#pragma unroll
+        for (int i = 0; i < NBT; ++i)
+#pragma unroll
+            for (int j = 0; j < NBT; ++j) acc[i][j] = d4{0, 0, 0, 0};
+        for (int s0 = 0; s0 < nsteps; s0 += KB) {
+            if (s0) load_block(s0);
+#pragma unroll
+            for (int u = 0; u < KB; ++u) {
+                if (u % 8 == 0 && s0 + u >= nsteps) break;  // uniform; the last 8 masked
+                const int a = 4 * (s0 + u) + lk, ac = min(a, nc4 - 1);
+                double av[NBT], b[NBT];
+#pragma unroll
+                for (int i = 0; i < NBT; ++i) {
+                    av[i] = Kt[ac * NBP + ((16 * i + lr) ^ (ac & 15))];
+                    b[i] = a < n_chi ? (double)bv[u][i] : 0.0;
+                }
+#pragma unroll
+                for (int i = 0; i < NBT; ++i)
+#pragma unroll
+                    for (int j = 0; j < NBT; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i], b[j], acc[i][j], 0, 0, 0);
+            }
+        }
+        // D layout of f64 16x16: Z[i = 16*ti + lk + 4r][j = 16*tj + lr]
+#pragma unroll
+        for (int i = 0; i < NBT; ++i)
+#pragma unroll
+            for (int j = 0; j < NBT; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) Z[(16 * i + lk + 4 * r) * NBP + 16 * j + lr] = acc[i][j][r];
+    }
+    // four consecutive multipoles of a pair leave together
+    __syncthreads();
+    for (int x = threadIdx.x; x < 4 * ntp; x += 256) {
+        const int e = x & 3, q = x >> 2;
+        if (io0 + e >= sel.n_out) continue;
+        int i, j;
+        pair_of(q, i, j);
+        const double *Ze = Zs + (size_t)e * NBP * NBP;
+        Ct[(size_t)q * sel.n_out + io0 + e] = pref[slot * n_ell + sel.idx[io0 + e]] * (Ze[i * NBP + j] + Ze[j * NBP + i]);
+    }
+}
+
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
 // ---------------------------------------------------------------------------------------------
@@ -3086,9 +3234,10 @@ struct Layout {
 // cosmologies per work-group of the adjoint's transposed contraction (their dw rows sit in LDS)
 constexpr int kAdjBT = 32;
 
-// Below this batch the fused kernel, which keeps one work-group per CU busy with a barrier per
-// b, streams the basis more slowly than the unfused contraction (many independent work-groups);
-// there the w round trip through HBM is the cheaper part.
+// Below this batch FP64 and FP32 stream the basis (stream.hip): there the basis is the traffic, and the
+// fused kernels, which keep one work-group per CU busy with a barrier per b, read it more slowly; from
+// here on two 16-cosmology tiles and more share every basis tile, and the fused kernels' LDS tiles pay.
+// The BF16 paths run unfused below it.
 constexpr int kFusedMinBatch = 32;
 
 // bins computed by the fused kernel (multiple of 4), 0 when it does not apply
@@ -3164,8 +3313,8 @@ hipError_t allow_large_lds() {
         const void *fns[] = {
             (const void *)quad_y_kernel<double, 16>, (const void *)quad_y_kernel<double, 32>,
             (const void *)quad_y_kernel<float, 16>, (const void *)quad_y_kernel<float, 32>,
-            (const void *)quad_c_mfma_kernel<double, 1>, (const void *)quad_c_mfma_kernel<double, 2>,
-            (const void *)quad_c_mfma_kernel<float, 1>, (const void *)quad_c_mfma_kernel<float, 2>,
+            (const void *)quad_c_mfma_kernel<double, 1>, (const void *)quad_c_few_kernel<double, 1>, (const void *)quad_c_mfma_kernel<double, 2>, (const void *)quad_c_few_kernel<double, 2>,
+            (const void *)quad_c_mfma_kernel<float, 1>, (const void *)quad_c_few_kernel<float, 1>, (const void *)quad_c_mfma_kernel<float, 2>, (const void *)quad_c_few_kernel<float, 2>,
             (const void *)adj_w_kernel<double, 16>, (const void *)adj_w_kernel<double, 32>,
             (const void *)adj_w_kernel<float, 16>, (const void *)adj_w_kernel<float, 32>,
             (const void *)contract_t_kernel<true>, (const void *)contract_t_kernel<false>,
@@ -3561,23 +3710,54 @@ void stage_contract_quad_f64(blast_plan *p, const blast_cl_args *a, const Ctx &x
     }
 }
 
-// stage 4: C = chi-quadrature and pair assembly
-void stage_quad_c(blast_plan *p, const blast_cl_args *a, const Ctx &x, const void *Y, hipStream_t s) {
+// stage 4: C = chi-quadrature and pair assembly of Y, the sum of nsplit ranges ysplit values apart
+struct YShape {
+    int nsplit;
+    size_t ysplit;
+};
+void stage_quad_c(blast_plan *p, const blast_cl_args *a, const Ctx &x, const void *Y, const YShape &sy, hipStream_t s) {
     Slots st{{p->tslot_type[0], p->tslot_type[1], p->tslot_type[2]}};
     const int nblk = (x.sel.n_out + kChiRows - 1) / kChiRows;
-    dim3 g2((unsigned)(p->nt * nblk), a->batch);
     const int nc4 = (p->n_chi + 3) & ~3;
     const size_t sh2 = ((size_t)x.nbp * nc4 + 4 * (size_t)x.nbp * x.nbp) * sizeof(double);
-#define BLAST_QC(YT, NB)                                                                                          \
-    hipLaunchKernelGGL((quad_c_mfma_kernel<YT, NB>), g2, dim3(256), sh2, s, (const YT *)Y, a->K_chi, p->d_wchi, \
-                       p->d_chi, p->d_pref, p->n_chi, p->rows_pad, p->n_ell, st, x.ng, x.ns, a->types, x.npairs,  \
-                       x.sel, a->C)
     const bool f64 = x.prec == BLAST_FP64;
-    if (f64 && x.nbp == 16) BLAST_QC(double, 1);
-    if (f64 && x.nbp == 32) BLAST_QC(double, 2);
-    if (!f64 && x.nbp == 16) BLAST_QC(float, 1);
-    if (!f64 && x.nbp == 32) BLAST_QC(float, 2);
-#undef BLAST_QC
+    // work-groups of 16 rows once they make four per CU, of 4 rows (one per wave) below: 16-row ones leave
+    // the chip idle there (37 cosmologies of 75 chi nodes x 69 rows: 10.4 us against 14.9)
+    const bool few = sy.nsplit > 1 || (long)p->nt * nblk * a->batch < 1024;
+    auto by_rows = [&](auto ytag, auto nbt) {
+        using YT = typename decltype(ytag)::type;
+        constexpr int NBT = decltype(nbt)::value;
+        if (few)
+            hipLaunchKernelGGL((quad_c_few_kernel<YT, NBT>), dim3((unsigned)(p->nt * ((x.sel.n_out + 3) / 4)), a->batch),
+                               dim3(256), sh2, s, (const YT *)Y, sy.nsplit, sy.ysplit, a->K_chi, p->d_wchi, p->d_chi,
+                               p->d_pref, p->n_chi, p->rows_pad, p->n_ell, st, x.ng, x.ns, a->types, x.npairs, x.sel,
+                               a->C);
+        else
+            hipLaunchKernelGGL((quad_c_mfma_kernel<YT, NBT>), dim3((unsigned)(p->nt * nblk), a->batch), dim3(256), sh2, s,
+                               (const YT *)Y, a->K_chi, p->d_wchi, p->d_chi, p->d_pref, p->n_chi, p->rows_pad, p->n_ell,
+                               st, x.ng, x.ns, a->types, x.npairs, x.sel, a->C);
+    };
+    auto by_bins = [&](auto ytag) {
+        if (x.nbp == 16) by_rows(ytag, std::integral_constant<int, 1>());
+        else by_rows(ytag, std::integral_constant<int, 2>());
+    };
+    if (f64) by_bins(TypeTag<double>());
+    else by_bins(TypeTag<float>());
+}
+
+// stages 2 + 3 of small batches on FP64 and FP32 (stream.hip)
+bool streams(int prec, int batch) { return (prec == BLAST_FP64 || prec == BLAST_FP32) && batch < kFusedMinBatch; }
+
+// the 16-row tiles that hold a requested multipole of a requested type
+RowTiles row_tiles(const blast_plan *p, const blast_cl_args *a, const Ctx &x, bool all) {
+    RowTiles r{};
+    bool need[3 * kMaxEll / 16] = {};
+    for (int sl = 0; sl < p->nt; ++sl)
+        if (p->tslot_type[sl] & a->types)
+            for (int i = 0; i < x.sel.n_out; ++i) need[(sl * p->n_ell + x.sel.idx[i]) / 16] = true;
+    for (int t = 0; t < p->rows_pad / 16; ++t)
+        if (all || need[t]) r.add(t);
+    return r;
 }
 
 // Device memory a call uses in place of plan-owned or caller scratch (the no-alloc entry point)
@@ -3640,6 +3820,7 @@ blast_status forward_impl(blast_plan *p, const blast_cl_args *a, hipStream_t s, 
     const bool keep_fused = !need_w && fused_keeps_w(x.prec, x.nbins, a->batch);
     const int fnb = need_w || keep_fused ? fused_nb(x.prec, x.nbins, a->batch) : 0;
     const bool f64f = need_w && x.prec == BLAST_FP64 && fused_f64(x.nbins, a->batch);
+    YShape sy{1, 0};
     mark(0);
     if (conv) {
         blast_cl_args ac = *a;
@@ -3659,13 +3840,43 @@ blast_status forward_impl(blast_plan *p, const blast_cl_args *a, hipStream_t s, 
         stage_r_weights64(p, a, x, (double *)(ws + L.kt), s);
         mark(2);
         stage_contract_quad_f64(p, a, x, c, (const double *)(ws + L.kt), (double *)Y, s);
+    } else if (streams(x.prec, a->batch)) {
+        const bool f64 = x.prec == BLAST_FP64;
+        StreamCall k{};
+        k.plan = p;
+        k.basis = f64 ? (const void *)(nodal ? p->basis.nf64 : p->basis.f64)
+                      : (const void *)(nodal ? p->basis.nf32 : p->basis.f32);
+        k.c = c;
+        k.cld = nodal ? p->n_cheb : p->nc_pad;
+        k.K_chi2 = a->K_chi2;
+        k.batch = a->batch;
+        k.nbins = x.nbins;
+        k.tiles = row_tiles(p, a, x, a->w_save || a->y_save);
+        if (f64 && need_w && !a->y_save) {
+            // grids with few waves sum ranges of R nodes apart (FP64; the FP32 sums keep their order), in the
+            // scratch that w would take.  The number of ranges is the plan's alone, so that a cosmology's
+            // result does not depend on the batch, the multipoles or (up to 16) the bins it comes with
+            const int waves = p->n_chi * (p->rows_pad / 16);
+            const int ns = std::min({(p->n_R + x.nbp) / x.nbp, 2048 / waves, p->n_R / 4});
+            if (ns > 1) {
+                sy = YShape{ns, (size_t)a->batch * p->rows_pad * p->n_chi * x.nbp};
+                Y = ws + L.w;
+            }
+        }
+        k.nsplit = sy.nsplit;
+        k.ybs = x.nbp;
+        k.ysplit = sy.ysplit;
+        k.Y = Y;
+        k.w_out = a->w_save;
+        mark(2);
+        stream_contract_quad(k, f64, s);
     } else {
         stage_contract(p, a, x, c, clo, w, s);
         mark(2);
         stage_quad_y(p, a, x, w, Y, s);
     }
     mark(3);
-    stage_quad_c(p, a, x, Y, s);
+    stage_quad_c(p, a, x, Y, sy, s);
     mark(4);
     BLAST_HIP_TRY(hipGetLastError());
     return BLAST_OK;

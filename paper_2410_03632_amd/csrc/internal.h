@@ -141,6 +141,28 @@ size_t forward_workspace_bytes(const blast_plan *p, int batch, int prec, int n_b
 void noalloc_init(int device);
 blast_status forward_noalloc(blast_plan *p, const blast_cl_args *a, hipStream_t s);
 
+// stream.hip: contraction and R-quadrature of small batches
+struct RowTiles {  // the 16-row tiles of the basis that a call computes, four to a word
+    int n;
+    uint32_t t[3 * kMaxEll / 64];
+    __host__ __device__ int tile(int i) const { return (int)(t[i >> 2] >> (8 * (i & 3)) & 255u); }
+    void add(int v) { t[n >> 2] |= (uint32_t)v << (8 * (n & 3)), ++n; }
+};
+struct StreamCall {
+    const blast_plan *plan;
+    const void *basis;  // FP64 row-major or FP32 tiled, matching c
+    const void *c;      // rows of cld elements per (cosmology, point)
+    int cld;
+    const double *K_chi2;
+    int batch, nbins;
+    RowTiles tiles;
+    int nsplit;         // ranges of R nodes summed apart: Y of range s at Y + s * ysplit
+    int ybs;            // bins per Y row
+    size_t ysplit;
+    void *Y, *w_out;    // w_out nullable
+};
+void stream_contract_quad(const StreamCall &k, bool f64, hipStream_t s);
+
 // limber.hip
 blast_status limber(blast_plan *p, const blast_limber_args *a, hipStream_t s);
 
