@@ -37,7 +37,8 @@ def nodal_path(prec, cfg):
     """Whether the library contracts the nodal basis (the DCT applied to the basis when the plan
     is made) with nodal P itself, with no projection per call: FP16X3 on FP32 P with
     n_cheb % 4 == 0 and at most 16 bins; FP32 on FP32 P with n_cheb % 4 == 0; FP64 on FP64 P with
-    n_cheb % 32 == 0 (the bench's P types)."""
+    n_cheb % 32 == 0 (the bench's P types; the library does so for every even n_cheb, which this
+    count of the work leaves at the projection's)."""
     if prec == "fp16x3":
         return cfg.n_cheb % 4 == 0 and cfg.n_g + cfg.n_s <= 16
     if prec == "fp32":

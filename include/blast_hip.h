@@ -78,8 +78,9 @@ typedef enum {
  * bins (P rows split into FP16 hi + lo inside the contraction kernel; with 17-20 bins P is
  * split by the coefficient-input conversion instead of projected); FP32 on FP32 P with
  * n_cheb % 4 == 0 (P rows read in place of the padded coefficient rows); FP64 on FP64 P
- * with n_cheb a multiple of 32 (P rows are then laid out as the coefficient rows).  The backward on such calls computes dP = B^T dw likewise.  The
- * result is that of the projection route up to rounding; on the ridge R ~ 1 the terms
+ * with an even n_cheb (likewise; a plan that has no room for the FP64 nodal basis and whose
+ * n_cheb is not a multiple of 32 does without it and projects).  The backward on such calls
+ * computes dP = B^T dw likewise (FP32: n_cheb a multiple of 32).  The result is that of the projection route up to rounding; on the ridge R ~ 1 the terms
  * B_j P_j are quadrature weights of one sign, so the sum cancels far less than the
  * Chebyshev terms do and the error of the mixed paths drops on the named workloads
  * (figures below; on small grids with k up to 0.6/Mpc the two routes trade places, both
@@ -273,7 +274,7 @@ blast_status blast_cl_forward_noalloc(blast_plan *plan, const blast_cl_args *arg
  * and dC = dL/dC (device, FP64, shaped like args->C) it enqueues on `stream`:
  *   dP      device, nullable, P's dtype and shape, 16-byte aligned: dL/dP (nodal values or
  *           coefficients per args->p_kind) -- the transposed contraction streams the basis again (on
- *           nodal P of the path's own type with n_cheb a multiple of 32 the nodal basis,
+ *           nodal P of the path's own type (FP32: n_cheb a multiple of 32) the nodal basis,
  *           whose product B^T dw is dP itself: FP64 reads the FP64 nodal basis, FP32 a
  *           transposed FP32 copy of it made at the first such call; otherwise Ttilde^T dw
  *           followed by the projection's adjoint);

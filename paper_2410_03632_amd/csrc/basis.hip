@@ -788,12 +788,19 @@ blast_status derive_precisions(blast_plan *p, hipStream_t s) {
                                p->rows_pad, p->nc_pad, p->n_cheb, nullptr, nullptr, nullptr, p->basis.nf32, nullptr);
         }
     }
-    if ((p->precisions & (1u << BLAST_FP64)) && p->n_cheb == p->nc_pad) {  // FP64 nodal P read as c
+    // FP64 nodal P read as c, in whole 16-byte granules.  (Unpadded rows can also be projected: a plan that
+    // has no room for the copy does without it.)
+    if ((p->precisions & (1u << BLAST_FP64)) && p->n_cheb % 2 == 0) {
         hipError_t e = hipMalloc(&p->basis.nf64, n * sizeof(double));
-        if (e != hipSuccess) return p->basis.nf64 = nullptr, fail(e, "FP64 nodal basis");
-        const unsigned g = (unsigned)std::min<size_t>((nrows + 3) / 4, 2048);
-        hipLaunchKernelGGL(to_nodal_kernel<64>, dim3(g), dim3(256), 0, s, p->basis.f64, p->d_dctn64, nrows,
-                           p->rows_pad, p->nc_pad, p->n_cheb, nullptr, nullptr, nullptr, nullptr, p->basis.nf64);
+        if (e != hipSuccess) {
+            p->basis.nf64 = nullptr;
+            if (p->n_cheb == p->nc_pad || e != hipErrorOutOfMemory) return fail(e, "FP64 nodal basis");
+            (void)hipGetLastError();
+        } else {
+            const unsigned g = (unsigned)std::min<size_t>((nrows + 3) / 4, 2048);
+            hipLaunchKernelGGL(to_nodal_kernel<64>, dim3(g), dim3(256), 0, s, p->basis.f64, p->d_dctn64, nrows,
+                               p->rows_pad, p->nc_pad, p->n_cheb, nullptr, nullptr, nullptr, nullptr, p->basis.nf64);
+        }
     }
     const bool want_hi = p->precisions & ((1u << BLAST_BF16) | (1u << BLAST_BF16X3));
     const bool want_lo = p->precisions & (1u << BLAST_BF16X3);

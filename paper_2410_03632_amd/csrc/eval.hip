@@ -521,7 +521,7 @@ __global__ __launch_bounds__(256) void contract_kernel(const typename Cfg<PREC>:
                                                        const float *__restrict__ scale,
                                                        const typename Cfg<PREC>::E *__restrict__ c,
                                                        const uint16_t *__restrict__ c_lo, int batch, int NP,
-                                                       int rows_pad, int ncp, void *__restrict__ w_out) {
+                                                       int rows_pad, int ncp, void *__restrict__ w_out, int cld) {
     using C = Cfg<PREC>;
     using E = typename C::E;
     using Acc = typename C::Acc;
@@ -544,7 +544,9 @@ __global__ __launch_bounds__(256) void contract_kernel(const typename Cfg<PREC>:
         const int bb = i / vec_per_row, v = i % vec_per_row;
         U4 val = {0u, 0u, 0u, 0u}, vlo = {0u, 0u, 0u, 0u};
         if (bb < nb) {
-            const size_t off = ((size_t)(beta0 + bb) * NP + ab) * ncp + (size_t)v * VEC;
+            // c rows of cld elements (ncp for the library's own c; n_cheb for a caller's nodal P, whose
+            // granules past its end repeat the last one: their basis columns are zero)
+            const size_t off = ((size_t)(beta0 + bb) * NP + ab) * cld + (size_t)min(v, cld / VEC - 1) * VEC;
             val = *(const U4 *)(c + off);
             if (X3) vlo = *(const U4 *)(c_lo + off);
         }
@@ -1942,7 +1944,7 @@ template <int NB, int KS, int NSTG>
 __global__ __launch_bounds__(512) void contract_quad_f64_kernel(const double *__restrict__ basis,
                                                                 const double *__restrict__ c,
                                                                 const double *__restrict__ Kt, int batch, int n_chi,
-                                                                int n_R, int rows_pad, int nBT, int units,
+                                                                int n_R, int rows_pad, int nBT, int units, int cld,
                                                                 double *__restrict__ Y) {
     using S = F64Shape<KS>;
     constexpr int ncp = KS * NSTG, NBK = 16, TR = kF64TR;
@@ -1972,7 +1974,10 @@ __global__ __launch_bounds__(512) void contract_quad_f64_kernel(const double *__
     const bool busy = rt0 + ti < RT && 16 * tj < nb;
 
     // DMA sources at b = 0, stage 0 (element offsets); rows past the end read the last valid row
+    // c rows have cld elements: ncp, or n_cheb for a caller's nodal P, whose granules past its end repeat the
+    // last one (their basis columns are zero)
     size_t srcA[S::A_PW], srcC[S::C_PW];
+    int grC[S::C_PW];
 #pragma unroll
     for (int k = 0; k < S::A_PW; ++k) {
         const int row = (w + k * S::NW) * S::RPC + lane / S::GR, gr = (lane % S::GR) ^ (row & 15);
@@ -1983,7 +1988,8 @@ __global__ __launch_bounds__(512) void contract_quad_f64_kernel(const double *__
     for (int k = 0; k < S::C_PW; ++k) {
         const int row = (w + k * S::NW) * S::RPC + lane / S::GR, gr = (lane % S::GR) ^ (row & 15);
         const size_t beta = (size_t)bt * 64 + min(row, nb - 1);
-        srcC[k] = (beta * NP + (size_t)a * n_R) * ncp + 2 * gr;
+        srcC[k] = (beta * NP + (size_t)a * n_R) * cld;
+        grC[k] = gr;
     }
     // weights: chunk w holds cosmologies 8w..8w+7 (128 bytes each), granule gk of cosmology cr in
     // slot (gk + cr / 2) % 8, so that the 16 cosmologies of a read fall in distinct banks
@@ -1995,11 +2001,11 @@ __global__ __launch_bounds__(512) void contract_quad_f64_kernel(const double *__
     auto dma = [&](int idx) {
         const int b = idx / NSTG, s = idx % NSTG;
         unsigned char *Ab = (idx & 1) ? A1 : A0, *Cb = (idx & 1) ? C1 : C0;
-        const size_t offA = (size_t)b * rows_pad * ncp + (size_t)s * KS, offC = (size_t)b * ncp + (size_t)s * KS;
+        const size_t offA = (size_t)b * rows_pad * ncp + (size_t)s * KS, offC = (size_t)b * cld;
 #pragma unroll
         for (int k = 0; k < S::A_PW; ++k) lds_dma16(basis + srcA[k] + offA, Ab + (size_t)(w + k * S::NW) * 1024);
 #pragma unroll
-        for (int k = 0; k < S::C_PW; ++k) lds_dma16(c + srcC[k] + offC, Cb + (size_t)(w + k * S::NW) * 1024);
+        for (int k = 0; k < S::C_PW; ++k) lds_dma16(c + srcC[k] + offC + 2 * min(s * (KS / 2) + grC[k], cld / 2 - 1), Cb + (size_t)(w + k * S::NW) * 1024);
         if (s == 0) lds_dma16(Kt + srcK + (size_t)b * batch * NBK, ((b & 1) ? K1 : K0) + (size_t)w * 1024);
     };
 
@@ -2930,7 +2936,7 @@ __global__ __launch_bounds__(256) void contract_t_kernel(const typename std::con
                                                              *__restrict__ dw,
                                                          int batch, int NP, int rows_pad, int ncp,
                                                          typename std::conditional<F64, double, float>::type
-                                                             *__restrict__ dc) {
+                                                             *__restrict__ dc, int ld) {
     using T = typename std::conditional<F64, double, float>::type;
     using Acc = typename std::conditional<F64, d4, f4>::type;
     constexpr int BT = F64 ? 32 : 64, BTN = BT / 16;
@@ -3009,7 +3015,7 @@ __global__ __launch_bounds__(256) void contract_t_kernel(const typename std::con
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int n = 16 * nt + (F64 ? lk + 4 * r : 4 * lk + r);
-                dc[((size_t)(beta0 + bb) * NP + ab) * ncp + n] = acc[i][j][r];
+                if (n < ld) dc[((size_t)(beta0 + bb) * NP + ab) * ld + n] = acc[i][j][r];
             }
         }
     }
@@ -3551,7 +3557,7 @@ void stage_contract(blast_plan *p, const blast_cl_args *a, const Ctx &x, const v
                                                : (const E *)p->basis.hi);
         if constexpr (PR == BLAST_FP64) {
             hipLaunchKernelGGL((contract_kernel<PR>), grid, dim3(256), sh, s, bas, p->basis.lo, p->basis.scale,
-                               (const E *)c, clo, a->batch, p->NP, p->rows_pad, ncp, w);
+                               (const E *)c, clo, a->batch, p->NP, p->rows_pad, ncp, w, x.direct ? p->n_cheb : ncp);
         } else {
             const int RT = p->rows_pad / 16;
             const int W = std::min((RT + kTilesPerWave - 1) / kTilesPerWave, 8);
@@ -3688,7 +3694,8 @@ void stage_contract_quad_f64(blast_plan *p, const blast_cl_args *a, const Ctx &x
         constexpr int NB = decltype(nbtag)::value, KS = decltype(kstag)::value, NSTG = decltype(nstag)::value;
         hipLaunchKernelGGL((contract_quad_f64_kernel<NB, KS, NSTG>), dim3(grid), dim3(512), 0, s,
                            x.nodal ? p->basis.nf64 : p->basis.f64,
-                           (const double *)c, Kt, a->batch, p->n_chi, p->n_R, p->rows_pad, nBT, units, Y);
+                           (const double *)c, Kt, a->batch, p->n_chi, p->n_R, p->rows_pad, nBT, units,
+                           x.direct ? p->n_cheb : p->nc_pad, Y);
     };
     using I32 = std::integral_constant<int, 32>;
     using I64 = std::integral_constant<int, 64>;
@@ -3786,8 +3793,7 @@ blast_status forward_impl(blast_plan *p, const blast_cl_args *a, hipStream_t s, 
     const bool need_w = a->w_save == nullptr;
     // nodal values: the nodal basis contracted with P itself (direct): FP16X3 on FP32 P (at most
     // 16 bins; P split in the kernel), FP32 on FP32 P (P rows of n_cheb % 4 == 0 elements read in
-    // place of c rows) and FP64 on FP64 P (P rows in the coefficient rows' layout: n_cheb ==
-    // nc_pad).  FP32 P on FP16X3 with more bins: the nodal basis, with P
+    // place of c rows) and FP64 on FP64 P (even n_cheb, likewise).  FP32 P on FP16X3 with more bins: the nodal basis, with P
     // split as coefficient input is (conv).  The BF16 paths keep the projection: with 8 or 16 bits
     // per operand and no row scale on P, the rounding of every P_j can cost more than the
     // cancellation the nodal sum saves (BF16X3 measured both better and worse than through c)
@@ -4041,15 +4047,16 @@ blast_status backward(blast_plan *p, const blast_cl_args *a, const double *dC, v
 #undef BLAST_ADJ
     if (dP) {
         const dim3 gt = point_tile_grid(p->NP, (a->batch + kAdjBT - 1) / kAdjBT);
-        // nodal P of the path's own type with n_cheb == nc_pad: dP = B^T dw with the nodal basis
-        // B = Ttilde D (the adjoint of the projection folded in), written straight into dP
-        const bool ndp = a->p_kind == 0 && p->n_cheb == p->nc_pad &&
-                         (f64 ? a->p_dtype == 0 && p->basis.nf64 : a->p_dtype == 1 && p->basis.nf32);
+        // nodal P of the path's own type: dP = B^T dw with the nodal basis B = Ttilde D (the adjoint of the
+        // projection folded in), written straight into dP (FP32: only where dP's rows are dc's, n_cheb == nc_pad)
+        const bool ndp = a->p_kind == 0 && (f64 ? a->p_dtype == 0 && p->basis.nf64
+                                                : a->p_dtype == 1 && p->basis.nf32 && p->n_cheb == p->nc_pad);
         void *dcn = ndp ? dP : dc;
         if (f64) {
             const size_t sht = (size_t)kAdjBT * (p->rows_pad + 1) * 8;
             hipLaunchKernelGGL((contract_t_kernel<true>), gt, dim3(256), sht, s, ndp ? p->basis.nf64 : p->basis.f64,
-                               (const double *)dw, a->batch, p->NP, p->rows_pad, p->nc_pad, (double *)dcn);
+                               (const double *)dw, a->batch, p->NP, p->rows_pad, p->nc_pad, (double *)dcn,
+                               ndp ? p->n_cheb : p->nc_pad);
         } else {
             // dc = Ttilde^T dw is the forward contraction's product with the transposed basis (rows of
             // Ttilde^T: the nc_pad Chebyshev columns; its K: the rows_pad basis rows) and dw in place of c
