@@ -3752,8 +3752,21 @@ void stage_quad_c(blast_plan *p, const blast_cl_args *a, const Ctx &x, const voi
     else by_bins(TypeTag<float>());
 }
 
-// stages 2 + 3 of small batches on FP64 and FP32 (stream.hip)
-bool streams(int prec, int batch) { return (prec == BLAST_FP64 || prec == BLAST_FP32) && batch < kFusedMinBatch; }
+// stages 2 + 3 by streaming the basis (stream.hip): FP64 and FP32 below kFusedMinBatch, and from there on
+// where the fused kernels (which then take the call otherwise, and whose FP32 sums the streaming kernel
+// repeats bit for bit) have too few work-groups for the chip.  Counted in the streaming kernel's waves, on
+// grids from 24 x 16 to 128 x 48 points at batches 33-256: FP32 1.06 to 2.1 times the fused kernel's speed up
+// to 2048 waves and 0.75-1.2 times above; FP64, whose fused kernel reuses a basis tile for 64 cosmologies
+// where this one reuses it for 16, 1.26 to 1.8 times up to 768 waves on two row tiles, 0.98-1.12 on four.
+// One row tile leaves three of four waves idle (0.6-1.06).
+bool streams(const blast_plan *p, const Ctx &x, int batch) {
+    if (x.prec != BLAST_FP64 && x.prec != BLAST_FP32) return false;
+    if (batch < kFusedMinBatch) return true;
+    if (x.nbins > (x.prec == BLAST_FP64 ? 16 : 20)) return false;
+    const int RT = p->rows_pad / 16;
+    const long waves = (long)p->n_chi * ((RT + 3) / 4 * 4) * ((batch + 15) / 16);
+    return RT > 1 && waves <= (x.prec == BLAST_FP64 ? 512 : 2048);
+}
 
 // the 16-row tiles that hold a requested multipole of a requested type
 RowTiles row_tiles(const blast_plan *p, const blast_cl_args *a, const Ctx &x, bool all) {
@@ -3824,8 +3837,9 @@ blast_status forward_impl(blast_plan *p, const blast_cl_args *a, hipStream_t s, 
     void *w = need_w ? (void *)(ws + L.w) : a->w_save;
     void *Y = a->y_save ? a->y_save : (void *)(ws + L.y);
     const bool keep_fused = !need_w && fused_keeps_w(x.prec, x.nbins, a->batch);
-    const int fnb = need_w || keep_fused ? fused_nb(x.prec, x.nbins, a->batch) : 0;
-    const bool f64f = need_w && x.prec == BLAST_FP64 && fused_f64(x.nbins, a->batch);
+    const bool stream = streams(p, x, a->batch);
+    const int fnb = !stream && (need_w || keep_fused) ? fused_nb(x.prec, x.nbins, a->batch) : 0;
+    const bool f64f = !stream && need_w && x.prec == BLAST_FP64 && fused_f64(x.nbins, a->batch);
     YShape sy{1, 0};
     mark(0);
     if (conv) {
@@ -3846,7 +3860,7 @@ blast_status forward_impl(blast_plan *p, const blast_cl_args *a, hipStream_t s, 
         stage_r_weights64(p, a, x, (double *)(ws + L.kt), s);
         mark(2);
         stage_contract_quad_f64(p, a, x, c, (const double *)(ws + L.kt), (double *)Y, s);
-    } else if (streams(x.prec, a->batch)) {
+    } else if (stream) {
         const bool f64 = x.prec == BLAST_FP64;
         StreamCall k{};
         k.plan = p;
@@ -3874,6 +3888,7 @@ blast_status forward_impl(blast_plan *p, const blast_cl_args *a, hipStream_t s, 
         k.ysplit = sy.ysplit;
         k.Y = Y;
         k.w_out = a->w_save;
+        k.two_chains = a->batch >= kFusedMinBatch;
         mark(2);
         stream_contract_quad(k, f64, s);
     } else {

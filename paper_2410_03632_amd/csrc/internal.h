@@ -160,6 +160,7 @@ struct StreamCall {
     int ybs;            // bins per Y row
     size_t ysplit;
     void *Y, *w_out;    // w_out nullable
+    bool two_chains;    // FP32: the fused kernel's summation order
 };
 void stream_contract_quad(const StreamCall &k, bool f64, hipStream_t s);
 

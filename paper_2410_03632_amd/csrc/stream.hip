@@ -49,7 +49,8 @@ __device__ inline void lds_barrier() {
 
 // NC: blocks of 32 columns (nc_pad / 32); BT cosmologies per tile; NBL bins per lane; NPU: nodes held by
 // the ring.
-template <typename T, int NC, int BT, int NBL, int NPU>
+// TWO: two accumulator chains, K slices 0, 2 and 1, 3 of every four, as contract_quad_kernel<FP32> sums them.
+template <typename T, int NC, int BT, int NBL, int NPU, bool TWO>
 __global__ __launch_bounds__(64 * kStreamWaves, 2) void stream_kernel(
     const T *__restrict__ basis, const T *__restrict__ c, int cld, const double *__restrict__ Kchi2,
     const double *__restrict__ wR, int batch, int nbins, int n_chi, int n_R, int rows_pad, RowTiles tiles, int nct,
@@ -171,7 +172,7 @@ __global__ __launch_bounds__(64 * kStreamWaves, 2) void stream_kernel(
         __builtin_amdgcn_sched_barrier(0);
         const T *cs = &Cs[i & 1][col * CST + lk * VEC];
         using Acc = typename std::conditional<F64, d4, f4>::type;
-        Acc acc = Acc{0, 0, 0, 0};
+        Acc acc = Acc{0, 0, 0, 0}, acc2 = Acc{0, 0, 0, 0};
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
             U4 cv[L];
@@ -186,12 +187,16 @@ __global__ __launch_bounds__(64 * kStreamWaves, 2) void stream_kernel(
                 } else {
                     const f4 x = __builtin_bit_cast(f4, A[nu][j][l]), z = __builtin_bit_cast(f4, cv[l]);
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u], z[u], acc, 0, 0, 0);
+                    for (int u = 0; u < 4; ++u) {
+                        Acc &to = TWO && (u & 1) ? acc2 : acc;
+                        to = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u], z[u], to, 0, 0, 0);
+                    }
                 }
             }
             load_A(nu, j, b + NPU);
             __builtin_amdgcn_sched_barrier(0);
         }
+        if constexpr (TWO) acc = acc + acc2;
         // a lane holds w of rows lk + 4 r (FP64) or 4 lk + r (FP32) of the tile for its cosmology
         if (w_out && active && lr < BT && beta < batch) {
             T *wo = w_out + ((size_t)beta * NP + (size_t)a * n_R + b) * rows_pad + 16 * rt;
@@ -254,15 +259,22 @@ __global__ __launch_bounds__(64 * kStreamWaves, 2) void stream_kernel(
 template <typename T>
 void launch(const StreamCall &k, hipStream_t s) {
     const blast_plan *p = k.plan;
-    auto go = [&](auto nct_, auto btt, auto nblt, auto nput) {
+    auto go2 = [&](auto nct_, auto btt, auto nblt, auto nput, auto twot) {
         constexpr int NC = decltype(nct_)::value, BT = decltype(btt)::value, NBL = decltype(nblt)::value;
         constexpr int NPU = decltype(nput)::value;
         const int nct = (k.batch + BT - 1) / BT, groups = (k.tiles.n + kStreamWaves - 1) / kStreamWaves;
         const int units = p->n_chi * k.nsplit * groups * nct;
-        hipLaunchKernelGGL((stream_kernel<T, NC, BT, NBL, NPU>), dim3((unsigned)((units + 7) / 8 * 8)),
+        hipLaunchKernelGGL((stream_kernel<T, NC, BT, NBL, NPU, decltype(twot)::value>), dim3((unsigned)((units + 7) / 8 * 8)),
                            dim3(64 * kStreamWaves), 0, s, (const T *)k.basis, (const T *)k.c, k.cld, k.K_chi2, p->d_wR,
                            k.batch, k.nbins, p->n_chi, p->n_R, p->rows_pad, k.tiles, nct, k.nsplit, units, k.ybs,
                            k.ysplit, (T *)k.Y, (T *)k.w_out);
+    };
+    // (only batches past the fused kernels' smallest take their two chains: the widest tiles)
+    auto go = [&](auto nct_, auto btt, auto nblt, auto nput) {
+        if constexpr (sizeof(T) == 4 && decltype(nblt)::value == 16) {
+            if (k.two_chains) return go2(nct_, btt, nblt, nput, std::true_type());
+        }
+        go2(nct_, btt, nblt, nput, std::false_type());
     };
     // rings as deep as the registers hold next to Y (256 per lane at two waves per SIMD)
     constexpr bool F64 = sizeof(T) == 8;

@@ -127,3 +127,37 @@ def test_stream_skips_rows_not_asked_for(prec, batch):
             got = plan.forward(*args, precision=prec, coef=True, workspace=ws, ell_idx=idx, types=types).cpu().numpy()
             want = full[:, sel][:, :, idx]
             assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("n_cheb", [32, 90])
+@pytest.mark.parametrize("batch,n_g,n_s", [(32, 3, 1), (33, 10, 5), (40, 16, 4), (100, 2, 2)])
+def test_small_grid_large_batch(prec, n_cheb, batch, n_g, n_s):
+    """From 32 cosmologies on, grids with few work-groups stream too: within the bound above, and on FP32
+    (whose order of summation is the fused kernel's) bitwise what a batch large enough for the fused
+    kernel gives the same cosmologies, w and Y included."""
+    plan, T = _plan(n_cheb, n_ell=9, n_chi=5, n_R=7)
+    nb = n_g + n_s
+    c, K, K2 = _inputs(plan, batch, nb, n_cheb + batch)
+    ref, S = _reference(plan, T, c, K, K2, n_g, n_s)
+    u = 2.0 ** (-53 if prec == "fp64" else -24)
+    tol = u * (plan.n_cheb + len(plan.R) + 8) * S + 2.0 ** -53 * (len(plan.chi) + 8) * S
+    run = lambda *x, **kw: plan.forward(_dev(x[0]), _dev(x[1]), _dev(x[2]), n_g, n_s, precision=prec, coef=True, **kw)
+    C = run(c, K, K2).cpu().numpy()
+    assert np.all(np.abs(C - ref) <= tol), np.max(np.abs(C - ref) / tol)
+    if prec == "fp32" and nb <= 20:
+        many = 16 * (2048 // (5 * 4)) + 32  # past the streaming kernel's waves
+        rep = lambda x: np.concatenate([x] * (many // batch + 1))[:many]
+        kept = []
+        for x in ((c, K, K2), (rep(c), rep(K), rep(K2))):
+            n = len(x[0])
+            w = torch.zeros(n * 35 * plan.rows_pad, dtype=torch.float32, device="cuda")
+            y = torch.zeros(plan.y_numel(n, nb), dtype=torch.float32, device="cuda")
+            Cn = run(*x, w_save=w, y_save=y)
+            yn = y.view(n, plan.rows_pad, 5, -1)
+            # an all-clustering or all-shear row keeps only its own bins' sums on the fused path
+            kept.append((Cn[:batch].clone(), w.view(n, -1)[:batch].clone(),
+                         yn[:batch, :9, :, :n_g].clone(), yn[:batch, 9:18, :, :nb].clone()))
+        for g, h in zip(*kept):
+            assert torch.equal(g, h)
+        assert np.array_equal(kept[0][0].cpu().numpy(), C)
