@@ -2715,60 +2715,90 @@ __global__ __launch_bounds__(256) void adj_dy_mfma_kernel(const double *__restri
     }
 }
 
-// dK_chi[beta][l][a] = wchi_a chi_a sum_{row, m} S[row][m][l] Y[row][a][m]
-// Work-group = (64 chi nodes, cosmology), 4 waves: lane = chi node, wave w takes rows w, w + 4, ...
-// and keeps NB sums (one per l).  A wave copies its row's S (NB x NB) into its own LDS slot with
-// coalesced loads and reads it back as broadcasts (every lane the same address); the row's Y
-// entries are 16-byte loads per lane.  The waves' sums are added in LDS in a fixed order.
-template <typename T, int NB>
-__global__ __launch_bounds__(256) void adj_kchi_kernel(const T *__restrict__ Y, const double *__restrict__ Sg,
-                                                       const double *__restrict__ wchi,
-                                                       const double *__restrict__ chi, int n_chi, int rows,
-                                                       int rows_pad, int nbins, double *__restrict__ dK) {
-    constexpr int KV = 16 / sizeof(T), SV = NB * NB / 2;  // 16-byte pieces of one S
-    __shared__ __align__(16) double Ss[4][NB * NB];
-    __shared__ double part[3][64][NB + 1];
+// dK_chi[beta][l][a] = wchi_a chi_a sum_{row, m} S[row][l][m] Y[row][a][m]  (S symmetric)
+// On FP64 MFMA: M = l, N = chi nodes, K = (row, m); MFMA e of a 16-bin group takes bin 4 lk + e from lane
+// group lk, so a lane reads its S and Y entries as 16-byte pieces and a wave whole rows of both.
+// Work-group = (16 AT chi nodes, cosmology), NW waves; wave w takes rows w, w + NW, ..., its next row's loads
+// in flight under the current row's MFMAs; the waves' sums are added in LDS in wave order.  Bound by reading
+// Y (302 MB at full 3x2pt, FP32, batch 64); the form with lanes over chi nodes read S back from LDS as
+// broadcasts, 128 reads per row and wave, and was bound by those.
+template <typename T, int NB, int AT, int NW>
+__global__ __launch_bounds__(64 * NW) void adj_kchi_kernel(const T *__restrict__ Y, const double *__restrict__ Sg,
+                                                           const double *__restrict__ wchi,
+                                                           const double *__restrict__ chi, int n_chi, int rows,
+                                                           int rows_pad, int nbins, double *__restrict__ dK) {
+    constexpr int NT = NB / 16, YV = 4 * (int)sizeof(T) / 16;  // bin tiles; 16-byte pieces of 4 Y values
+    constexpr int PS = 16 * AT + 1;
+    __shared__ double part[NW][NB][PS];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int beta = blockIdx.y;
-    const int a = blockIdx.x * 64 + lane, ac = min(a, n_chi - 1);
-    double *sw = Ss[w];
-    double acc[NB];
+    const int lr = lane & 15, lk = lane >> 4;
+    const int beta = blockIdx.y, a0 = blockIdx.x * 16 * AT;
+    const double *sg = Sg + (size_t)beta * rows_pad * NB * NB;
+    const T *yb = Y + (size_t)beta * rows_pad * n_chi * NB;
+    d4 acc[NT][AT];
 #pragma unroll
-    for (int l = 0; l < NB; ++l) acc[l] = 0.0;
-    for (int row = w; row < rows; row += 4) {
-        const double *sg = Sg + ((size_t)beta * rows_pad + row) * NB * NB;
-        const T *y = Y + (((size_t)beta * rows_pad + row) * n_chi + ac) * NB;
-        T yv[NB];
+    for (int i = 0; i < NT; ++i)
 #pragma unroll
-        for (int q = 0; q < NB; q += KV) *(U4 *)(yv + q) = *(const U4 *)(y + q);
+        for (int t = 0; t < AT; ++t) acc[i][t] = d4{0, 0, 0, 0};
+    struct Row {
+        U4 s[NT][NT][2], y[NT][AT][YV];
+    };
+    auto load = [&](int row, Row &q) {
+        const double *sr = sg + (size_t)row * NB * NB;
+        const T *yr = yb + (size_t)row * n_chi * NB;
 #pragma unroll
-        for (int q = lane; q < SV; q += 64) *(U4 *)(sw + 2 * q) = *(const U4 *)(sg + 2 * q);
-        // the slot's writes are done before any lane reads them (LDS accesses of a wave complete
-        // in order; the asm also keeps the compiler from moving accesses across it)
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        for (int h = 0; h < NT; ++h) {
 #pragma unroll
-        for (int m = 0; m < NB; ++m) {
-            const double ym = (double)yv[m];
+            for (int i = 0; i < NT; ++i)
 #pragma unroll
-            for (int l = 0; l < NB; l += 2) {
-                const double2 sv = *(const double2 *)(sw + m * NB + l);
-                acc[l] = fma(sv.x, ym, acc[l]);
-                acc[l + 1] = fma(sv.y, ym, acc[l + 1]);
-            }
+                for (int v = 0; v < 2; ++v) q.s[i][h][v] = *(const U4 *)(sr + (16 * i + lr) * NB + 16 * h + 4 * lk + 2 * v);
+#pragma unroll
+            for (int t = 0; t < AT; ++t)
+#pragma unroll
+                for (int v = 0; v < YV; ++v)
+                    q.y[h][t][v] = *(const U4 *)(yr + (size_t)min(a0 + 16 * t + lr, n_chi - 1) * NB + 16 * h + 4 * lk +
+                                                 v * (16 / (int)sizeof(T)));
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // reads done before the next row's writes
+    };
+    auto run = [&](const Row &q) {
+#pragma unroll
+        for (int h = 0; h < NT; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int t = 0; t < AT; ++t) {
+                    const double y = (double)((const T *)&q.y[h][t][0])[e];
+#pragma unroll
+                    for (int i = 0; i < NT; ++i)
+                        acc[i][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(((const double *)&q.s[i][h][0])[e], y, acc[i][t],
+                                                                         0, 0, 0);
+                }
+    };
+    Row q0, q1;
+    if (w < rows) load(w, q0);
+    for (int row = w; row < rows; row += 2 * NW) {
+        load(min(row + NW, rows - 1), q1);
+        __builtin_amdgcn_sched_barrier(0);
+        run(q0);
+        load(min(row + 2 * NW, rows - 1), q0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (row + NW < rows) run(q1);
     }
-    if (w > 0)
+    // lane holds l = 16 i + lk + 4 r of node 16 t + lr
 #pragma unroll
-        for (int l = 0; l < NB; ++l) part[w - 1][lane][l] = acc[l];
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int t = 0; t < AT; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) part[w][16 * i + lk + 4 * r][16 * t + lr] = acc[i][t][r];
     __syncthreads();
-    if (w == 0 && a < n_chi) {
-        const double f = wchi[a] * chi[a];
+    for (int x = threadIdx.x; x < nbins * 16 * AT; x += 64 * NW) {
+        const int l = x / (16 * AT), al = x % (16 * AT), a = a0 + al;
+        if (a >= n_chi) continue;
+        double v = part[0][l][al];
 #pragma unroll
-        for (int l = 0; l < NB; ++l)
-            if (l < nbins)
-                dK[((size_t)beta * nbins + l) * n_chi + a] =
-                    f * (((acc[l] + part[0][lane][l]) + part[1][lane][l]) + part[2][lane][l]);
+        for (int u = 1; u < NW; ++u) v += part[u][l][al];
+        dK[((size_t)beta * nbins + l) * n_chi + a] = wchi[a] * chi[a] * v;
     }
 }
 
@@ -2780,16 +2810,30 @@ __global__ __launch_bounds__(256) void adj_kchi_kernel(const T *__restrict__ Y, 
 template <int NB>
 constexpr int adj_w_stride() { return NB + 1; }
 
+// Work-group -> (chi_a, cosmology) over a 1-D grid of chi_cosmology_grid(n_chi, batch) work-groups: each XCD
+// (work-groups go round-robin over 8) gets a run of neighbouring chi nodes, whose dY rows are the two halves
+// of the same 128-byte lines.
+__device__ inline bool chi_cosmology(int n_chi, int batch, int &a, int &beta) {
+    const int units = n_chi * batch, per = (units + 7) / 8;
+    const int u = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+    if ((int)(blockIdx.x / 8) >= per || u >= units) return false;
+    a = u % n_chi;
+    beta = u / n_chi;
+    return true;
+}
+inline dim3 chi_cosmology_grid(int n_chi, int batch) { return dim3((unsigned)((n_chi * batch + 7) / 8 * 8)); }
+
 template <typename T, int NB>
 __global__ __launch_bounds__(256) void adj_w_kernel(const T *__restrict__ dY, const T *__restrict__ w,
                                                     const double *__restrict__ Kchi2, const double *__restrict__ wR,
-                                                    int NP, int nR, int n_chi, int rows, int rows_pad, int nbins,
-                                                    T *__restrict__ dw, double *__restrict__ dK2) {
+                                                    int batch, int NP, int nR, int n_chi, int rows, int rows_pad,
+                                                    int nbins, T *__restrict__ dw, double *__restrict__ dK2) {
     constexpr int DS = adj_w_stride<NB>();
     extern __shared__ __align__(16) unsigned char smem_a[];
     double *Kh = (double *)smem_a;                   // [nR][NB]
     double *dYa = Kh + (size_t)nR * NB;              // [rows_pad][DS]
-    const int a = blockIdx.x, beta = blockIdx.y;
+    int a, beta;
+    if (!chi_cosmology(n_chi, batch, a, beta)) return;  // uniform over the work-group
     for (int i = threadIdx.x; i < nR * NB; i += blockDim.x) {
         const int b = i / NB, m = i % NB;
         Kh[i] = m < nbins ? wR[b] * Kchi2[(((size_t)beta * nbins + m) * n_chi + a) * nR + b] : 0.0;
@@ -2838,15 +2882,16 @@ __global__ __launch_bounds__(256) void adj_w_kernel(const T *__restrict__ dY, co
 template <int NB>
 __global__ __launch_bounds__(256) void adj_w_mfma_kernel(const float *__restrict__ dY, const float *__restrict__ w,
                                                          const double *__restrict__ Kchi2,
-                                                         const double *__restrict__ wR, int NP, int nR, int n_chi,
-                                                         int rows, int rows_pad, int nbins, float *__restrict__ dw,
-                                                         double *__restrict__ dK2) {
+                                                         const double *__restrict__ wR, int batch, int NP, int nR,
+                                                         int n_chi, int rows, int rows_pad, int nbins,
+                                                         float *__restrict__ dw, double *__restrict__ dK2) {
     extern __shared__ __align__(16) unsigned char smem_aw[];
     const int nRt = (nR + 15) / 16, nRp = 16 * nRt;
     float *Kh = (float *)smem_aw;                 // [nRp][NB]
     float *dYt = Kh + (size_t)nRp * NB;            // [NB][rows_pad + 4]
     const int ds = rows_pad + 4;
-    const int a = blockIdx.x, beta = blockIdx.y;
+    int a, beta;
+    if (!chi_cosmology(n_chi, batch, a, beta)) return;  // uniform over the work-group
     for (int i = threadIdx.x; i < nRp * NB; i += blockDim.x) {
         const int b = i / NB, m = i % NB;
         Kh[i] = (b < nR && m < nbins) ? (float)(wR[b] * Kchi2[(((size_t)beta * nbins + m) * n_chi + a) * nR + b])
@@ -2927,19 +2972,105 @@ __global__ __launch_bounds__(256) void adj_w_mfma_kernel(const float *__restrict
     }
 }
 
+// FP64 path of adj_w_kernel on MFMA (v_mfma_f64_16x16x4_f64): the two products of adj_w_mfma_kernel with the
+// same K orders (MFMA e of 16 bins, or of 16 rows, takes 4 lk + e from lane group lk, so operands are read as
+// 16-byte pieces) and MFMA row lk + 4 r holding row (or node) 4 lk + r, so that a lane's four results are
+// neighbours and leave as 16-byte stores.  At full 3x2pt, batch 8, bound by w in and dw out (0.9 GB).
+template <int NB>
+__global__ __launch_bounds__(256) void adj_w64_mfma_kernel(const double *__restrict__ dY, const double *__restrict__ w,
+                                                           const double *__restrict__ Kchi2,
+                                                           const double *__restrict__ wR, int batch, int NP, int nR,
+                                                           int n_chi, int rows, int rows_pad, int nbins,
+                                                           double *__restrict__ dw, double *__restrict__ dK2) {
+    constexpr int KS = NB + 2, NQ = NB / 16;
+    extern __shared__ __align__(16) unsigned char smem_a64[];
+    const int nRt = (nR + 15) / 16, nRp = 16 * nRt, RTn = rows_pad / 16, ds = rows_pad + 2;
+    double *Kh = (double *)smem_a64;             // [nRp][KS]
+    double *dYt = Kh + (size_t)nRp * KS;         // [NB][ds]
+    int a, beta;
+    if (!chi_cosmology(n_chi, batch, a, beta)) return;  // uniform over the work-group
+    for (int i = threadIdx.x; i < nRp * NB; i += 256) {
+        const int b = i % nRp, m = i / nRp;
+        Kh[b * KS + m] = (b < nR && m < nbins) ? wR[b] * Kchi2[(((size_t)beta * nbins + m) * n_chi + a) * nR + b] : 0.0;
+    }
+    const double *dya = dY + ((size_t)beta * rows_pad * n_chi + a) * NB;  // + row * n_chi * NB + m (rows < rows)
+    for (int i = threadIdx.x; i < rows_pad * NB; i += 256) {
+        const int row = i / NB, m = i % NB;
+        dYt[(size_t)m * ds + row] = row < rows ? dya[(size_t)row * n_chi * NB + m] : 0.0;
+    }
+    __syncthreads();
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int lr = lane & 15, lk = lane >> 4, pr = 4 * (lr & 3) + (lr >> 2);
+    const size_t base = ((size_t)beta * NP + (size_t)a * nR) * rows_pad;  // w, dw of node b: + b * rows_pad
+    for (int tile = wv; tile < RTn * nRt; tile += 4) {
+        const int rt = tile % RTn, bt = tile / RTn;
+        d4 acc = {0, 0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const double *yt = dYt + (size_t)(16 * q + 4 * lk) * ds + 16 * rt + pr;
+            const double2 k0 = *(const double2 *)(Kh + (16 * bt + lr) * KS + 16 * q + 4 * lk);
+            const double2 k1 = *(const double2 *)(Kh + (16 * bt + lr) * KS + 16 * q + 4 * lk + 2);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(yt[0], k0.x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(yt[ds], k0.y, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(yt[2 * ds], k1.x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(yt[3 * ds], k1.y, acc, 0, 0, 0);
+        }
+        const int b = 16 * bt + lr;
+        if (b < nR) {
+            double *o = dw + base + (size_t)b * rows_pad + 16 * rt + 4 * lk;
+            *(double2 *)o = make_double2(acc[0], acc[1]);
+            *(double2 *)(o + 2) = make_double2(acc[2], acc[3]);
+        }
+    }
+    if (!dK2) return;
+    for (int bt = wv; bt < nRt; bt += 4) {
+        const double *wr = w + base + (size_t)min(16 * bt + pr, nR - 1) * rows_pad + 4 * lk;
+        d4 acc[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) acc[q] = d4{0, 0, 0, 0};
+        constexpr int CH = 4;  // 16-row steps of w in flight
+        for (int c0 = 0; c0 < RTn; c0 += CH) {
+            double2 x[CH][2];
+#pragma unroll
+            for (int u = 0; u < CH; ++u)
+#pragma unroll
+                for (int v = 0; v < 2; ++v) x[u][v] = *(const double2 *)(wr + 16 * min(c0 + u, RTn - 1) + 2 * v);
+#pragma unroll
+            for (int u = 0; u < CH; ++u) {
+                if (c0 + u >= RTn) break;
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    const double *yt = dYt + (size_t)(16 * q + lr) * ds + 16 * (c0 + u) + 4 * lk;
+                    const double2 y0 = *(const double2 *)yt, y1 = *(const double2 *)(yt + 2);
+                    acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u][0].x, y0.x, acc[q], 0, 0, 0);
+                    acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u][0].y, y0.y, acc[q], 0, 0, 0);
+                    acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u][1].x, y1.x, acc[q], 0, 0, 0);
+                    acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u][1].y, y1.y, acc[q], 0, 0, 0);
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int m = 16 * q + lr;
+            if (m >= nbins) continue;
+            double *o = dK2 + (((size_t)beta * nbins + m) * n_chi + a) * nR;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int b = 16 * bt + 4 * lk + r;
+                if (b < nR) o[b] = wR[b] * acc[q][r];
+            }
+        }
+    }
+}
+
 // transpose contraction: dc[beta][ab][n] = sum_row Ttilde[ab][row][n] dw[beta][ab][row]
 // M = n (wave w owns n tiles w, w+4), N = cosmologies (BT), K = rows, on MFMA.
-template <bool F64>
-__global__ __launch_bounds__(256) void contract_t_kernel(const typename std::conditional<F64, double, float>::type
-                                                             *__restrict__ basis,
-                                                         const typename std::conditional<F64, double, float>::type
-                                                             *__restrict__ dw,
-                                                         int batch, int NP, int rows_pad, int ncp,
-                                                         typename std::conditional<F64, double, float>::type
-                                                             *__restrict__ dc, int ld) {
-    using T = typename std::conditional<F64, double, float>::type;
-    using Acc = typename std::conditional<F64, d4, f4>::type;
-    constexpr int BT = F64 ? 32 : 64, BTN = BT / 16;
+template <int BT>
+__global__ __launch_bounds__(256) void contract_t_kernel(const double *__restrict__ basis,
+                                                         const double *__restrict__ dw, int batch, int NP,
+                                                         int rows_pad, int ncp, double *__restrict__ dc, int ld) {
+    using T = double;
+    constexpr int BTN = BT / 16;
     extern __shared__ __align__(16) unsigned char smem_t[];
     const int dst = rows_pad + 1;
     T *ws = (T *)smem_t;  // [BT][rows_pad + 1]
@@ -2947,20 +3078,26 @@ __global__ __launch_bounds__(256) void contract_t_kernel(const typename std::con
     if (!point_tile(NP, (batch + BT - 1) / BT, ab, tile)) return;  // uniform over the work-group
     const int beta0 = tile * BT;
     const int nb = min(BT, batch - beta0);
-    for (int i = threadIdx.x; i < BT * rows_pad; i += blockDim.x) {
-        const int bb = i / rows_pad, row = i % rows_pad;
-        ws[bb * dst + row] = bb < nb ? dw[((size_t)(beta0 + bb) * NP + ab) * rows_pad + row] : (T)0;
-    }
-    __syncthreads();
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int lr = lane & 15, lk = lane >> 4;
+    // wave wv takes cosmologies wv, wv + 4, ..., a lane two consecutive rows
+    for (int r0 = 2 * lane; r0 < rows_pad; r0 += 128)
+#pragma unroll
+        for (int u = 0; u < BT / 4; ++u) {
+            const int bb = 4 * u + wv;
+            double2 v = make_double2(0.0, 0.0);
+            if (bb < nb) v = *(const double2 *)(dw + ((size_t)(beta0 + bb) * NP + ab) * rows_pad + r0);
+            ws[bb * dst + r0] = v.x;
+            ws[bb * dst + r0 + 1] = v.y;
+        }
+    __syncthreads();
     const int NT = ncp >> 4;
-    const T *bp = basis + (size_t)ab * rows_pad * ncp;  // FP64: row-major; FP32: tiled layout
-    Acc acc[2][BTN];
+    const T *bp = basis + (size_t)ab * rows_pad * ncp;
+    d4 acc[2][BTN];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < BTN; ++j) acc[i][j] = Acc{0, 0, 0, 0};
+        for (int j = 0; j < BTN; ++j) acc[i][j] = d4{0, 0, 0, 0};
     // K steps of 4 rows in groups of 4 (rows_pad / 4 is a multiple of 4); the basis values of the
     // next group are loaded while the current one runs on the MFMA units
     const int S4 = rows_pad / 4;
@@ -2971,8 +3108,7 @@ __global__ __launch_bounds__(256) void contract_t_kernel(const typename std::con
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const int nt = wv + 4 * i;
-                const size_t o = F64 ? (size_t)row * ncp + 16 * nt + lr : tiled_off(row, 16 * nt + lr, ncp / 16, 4);
-                av[u][i] = nt < NT ? bp[o] : (T)0;
+                av[u][i] = nt < NT ? bp[(size_t)row * ncp + 16 * nt + lr] : (T)0;
             }
         }
     };
@@ -2987,10 +3123,7 @@ __global__ __launch_bounds__(256) void contract_t_kernel(const typename std::con
             for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int j = 0; j < BTN; ++j) {
-                    if constexpr (F64)
-                        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u][i], bv[j], acc[i][j], 0, 0, 0);
-                    else
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][i], bv[j], acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u][i], bv[j], acc[i][j], 0, 0, 0);
                 }
         }
     };
@@ -3014,7 +3147,7 @@ __global__ __launch_bounds__(256) void contract_t_kernel(const typename std::con
             if (bb >= nb) continue;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int n = 16 * nt + (F64 ? lk + 4 * r : 4 * lk + r);
+                const int n = 16 * nt + lk + 4 * r;
                 if (n < ld) dc[((size_t)(beta0 + bb) * NP + ab) * ld + n] = acc[i][j][r];
             }
         }
@@ -3322,8 +3455,8 @@ hipError_t allow_large_lds() {
             (const void *)quad_c_mfma_kernel<double, 1>, (const void *)quad_c_few_kernel<double, 1>, (const void *)quad_c_mfma_kernel<double, 2>, (const void *)quad_c_few_kernel<double, 2>,
             (const void *)quad_c_mfma_kernel<float, 1>, (const void *)quad_c_few_kernel<float, 1>, (const void *)quad_c_mfma_kernel<float, 2>, (const void *)quad_c_few_kernel<float, 2>,
             (const void *)adj_w_kernel<double, 16>, (const void *)adj_w_kernel<double, 32>,
-            (const void *)adj_w_kernel<float, 16>, (const void *)adj_w_kernel<float, 32>,
-            (const void *)contract_t_kernel<true>, (const void *)contract_t_kernel<false>,
+            (const void *)adj_w64_mfma_kernel<16>, (const void *)adj_w64_mfma_kernel<32>,
+            (const void *)contract_t_kernel<16>, (const void *)contract_t_kernel<kAdjBT>,
             (const void *)adj_project_split64_kernel<double, 4>, (const void *)adj_project_split64_kernel<float, 4>,
             (const void *)adj_project_split64_kernel<double, 3>, (const void *)adj_project_split64_kernel<float, 3>,
             (const void *)adj_w_mfma_kernel<16>, (const void *)adj_w_mfma_kernel<32>,
@@ -4038,20 +4171,33 @@ blast_status backward(blast_plan *p, const blast_cl_args *a, const double *dC, v
                                p->d_pref, p->n_chi, p->rows_pad, p->n_ell, sl, x.ng, x.ns, a->types, x.npairs,    \
                                x.sel.n_out, x.inv, (T *)dY, Sg);                                                  \
         if (dK_chi) {                                                                                             \
-            dim3 gk((unsigned)((p->n_chi + 63) / 64), a->batch);                                                  \
-            hipLaunchKernelGGL((adj_kchi_kernel<T, NB>), gk, dim3(256), 0, s, (const T *)Y, Sg, p->d_wchi,        \
-                               p->d_chi, p->n_chi, p->rows, p->rows_pad, x.nbins, dK_chi);                        \
+            /* 64 chi nodes per work-group once that makes one per CU, else 16 with the rows over 8 waves */      \
+            if ((long)((p->n_chi + 63) / 64) * a->batch >= 256)                                                   \
+                hipLaunchKernelGGL((adj_kchi_kernel<T, NB, 64 / NB, 4>),                                          \
+                                   dim3((unsigned)((p->n_chi + 1024 / NB - 1) / (1024 / NB)), a->batch), dim3(256), 0, s, \
+                                   (const T *)Y, Sg, p->d_wchi, p->d_chi, p->n_chi, p->rows, p->rows_pad, x.nbins, dK_chi); \
+            else                                                                                                  \
+                hipLaunchKernelGGL((adj_kchi_kernel<T, NB, 1, 8>), dim3((unsigned)((p->n_chi + 15) / 16), a->batch), \
+                                   dim3(512), 0, s, (const T *)Y, Sg, p->d_wchi, p->d_chi, p->n_chi, p->rows,     \
+                                   p->rows_pad, x.nbins, dK_chi);                                                 \
         }                                                                                                         \
-        dim3 gw(p->n_chi, a->batch);                                                                              \
+        const dim3 gw = chi_cosmology_grid(p->n_chi, a->batch);                                                   \
         if constexpr (std::is_same<T, float>::value) {                                                           \
             const size_t shw = ((size_t)((p->n_R + 15) / 16 * 16) * NB + (size_t)NB * (p->rows_pad + 4)) * 4;    \
             hipLaunchKernelGGL((adj_w_mfma_kernel<NB>), gw, dim3(256), shw, s, (const float *)dY,               \
-                               (const float *)w, a->K_chi2, p->d_wR, p->NP, p->n_R, p->n_chi, p->rows,          \
+                               (const float *)w, a->K_chi2, p->d_wR, a->batch, p->NP, p->n_R, p->n_chi, p->rows, \
                                p->rows_pad, x.nbins, (float *)dw, dK_chi2);                                     \
         } else {                                                                                                  \
+            const size_t shm = ((size_t)((p->n_R + 15) / 16 * 16) * (NB + 2) + (size_t)NB * (p->rows_pad + 2)) * 8; \
             const size_t shw = ((size_t)p->n_R * NB + (size_t)p->rows_pad * adj_w_stride<NB>()) * sizeof(double); \
+            /* the padded tables of the MFMA form are a little larger: the few shapes they do not fit */           \
+            if (shm <= 160 * 1024)                                                                                \
+                hipLaunchKernelGGL((adj_w64_mfma_kernel<NB>), gw, dim3(256), shm, s, (const double *)dY,          \
+                                   (const double *)w, a->K_chi2, p->d_wR, a->batch, p->NP, p->n_R, p->n_chi,      \
+                                   p->rows, p->rows_pad, x.nbins, (double *)dw, dK_chi2);                         \
+            else                                                                                                  \
             hipLaunchKernelGGL((adj_w_kernel<T, NB>), gw, dim3(256), shw, s, (const T *)dY, (const T *)w,       \
-                               a->K_chi2, p->d_wR, p->NP, p->n_R, p->n_chi, p->rows, p->rows_pad, x.nbins,      \
+                               a->K_chi2, p->d_wR, a->batch, p->NP, p->n_R, p->n_chi, p->rows, p->rows_pad, x.nbins, \
                                (T *)dw, dK_chi2);                                                               \
         }                                                                                                         \
     } while (0)
@@ -4068,10 +4214,16 @@ blast_status backward(blast_plan *p, const blast_cl_args *a, const double *dC, v
                                                 : a->p_dtype == 1 && p->basis.nf32 && p->n_cheb == p->nc_pad);
         void *dcn = ndp ? dP : dc;
         if (f64) {
-            const size_t sht = (size_t)kAdjBT * (p->rows_pad + 1) * 8;
-            hipLaunchKernelGGL((contract_t_kernel<true>), gt, dim3(256), sht, s, ndp ? p->basis.nf64 : p->basis.f64,
-                               (const double *)dw, a->batch, p->NP, p->rows_pad, p->nc_pad, (double *)dcn,
-                               ndp ? p->n_cheb : p->nc_pad);
+            // 16 cosmologies per work-group where that is all of them: half the MFMAs and half the LDS
+            const double *bas = ndp ? p->basis.nf64 : p->basis.f64;
+            const int ld = ndp ? p->n_cheb : p->nc_pad;
+            if (a->batch <= 16)
+                hipLaunchKernelGGL((contract_t_kernel<16>), point_tile_grid(p->NP, 1), dim3(256),
+                                   (size_t)16 * (p->rows_pad + 1) * 8, s, bas, (const double *)dw, a->batch, p->NP,
+                                   p->rows_pad, p->nc_pad, (double *)dcn, ld);
+            else
+                hipLaunchKernelGGL((contract_t_kernel<kAdjBT>), gt, dim3(256), (size_t)kAdjBT * (p->rows_pad + 1) * 8, s,
+                                   bas, (const double *)dw, a->batch, p->NP, p->rows_pad, p->nc_pad, (double *)dcn, ld);
         } else {
             // dc = Ttilde^T dw is the forward contraction's product with the transposed basis (rows of
             // Ttilde^T: the nc_pad Chebyshev columns; its K: the rows_pad basis rows) and dw in place of c

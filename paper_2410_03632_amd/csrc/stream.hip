@@ -85,8 +85,10 @@ __global__ __launch_bounds__(64 * kStreamWaves, 2) void stream_kernel(
     // the wave's tile of node b0, piece p of the lane at + p * PST, node b at + (b - b0) * nst
     constexpr int PST = F64 ? 4 : 64;
     const size_t nst = (size_t)rows_pad * ncp / VEC;
+    // (FP64: MFMA row lk + 4 r, which lane group lk holds in register r, is row 4 lk + r of the tile, so that a
+    // lane's four w are neighbours as they are on FP32)
     const U4 *pa = (const U4 *)basis + ((size_t)a * n_R + b0) * nst +
-                   (F64 ? (size_t)(16 * rt + lr) * GPR + lk : (size_t)rt * GPR * 16 + lane);
+                   (F64 ? (size_t)(16 * rt + 4 * (lr & 3) + (lr >> 2)) * GPR + lk : (size_t)rt * GPR * 16 + lane);
     U4 A[NPU][NC][L];
     auto load_A = [&](int nu, int j, int b) {
         const U4 *q = pa + (size_t)(min(b, b1 - 1) - b0) * nst;
@@ -197,14 +199,14 @@ __global__ __launch_bounds__(64 * kStreamWaves, 2) void stream_kernel(
             __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (TWO) acc = acc + acc2;
-        // a lane holds w of rows lk + 4 r (FP64) or 4 lk + r (FP32) of the tile for its cosmology
+        // a lane holds w of rows 4 lk + r of the tile for its cosmology
         if (w_out && active && lr < BT && beta < batch) {
-            T *wo = w_out + ((size_t)beta * NP + (size_t)a * n_R + b) * rows_pad + 16 * rt;
+            T *wo = w_out + ((size_t)beta * NP + (size_t)a * n_R + b) * rows_pad + 16 * rt + 4 * lk;
             if constexpr (F64) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) wo[lk + 4 * r] = acc[r];
+                *(double2 *)wo = make_double2(acc[0], acc[1]);
+                *(double2 *)(wo + 2) = make_double2(acc[2], acc[3]);
             } else {
-                *(float4 *)(wo + 4 * lk) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+                *(float4 *)wo = make_float4(acc[0], acc[1], acc[2], acc[3]);
             }
         }
         const T *ks = &Ks[((i % CB) * BT + col) * KST + bin0];
@@ -242,7 +244,7 @@ __global__ __launch_bounds__(64 * kStreamWaves, 2) void stream_kernel(
     if (!active || beta >= batch) return;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int row = 16 * rt + (F64 ? lk + 4 * r : 4 * lk + r);
+        const int row = 16 * rt + 4 * lk + r;
         T *yp = Y + (size_t)sp * ysplit + (((size_t)beta * rows_pad + row) * n_chi + a) * ybs + bin0;
 #pragma unroll
         for (int q0 = 0; q0 < NBL; q0 += VEC) {
