@@ -9,7 +9,7 @@
 // arrival order into the forming set while the launch they would make still fits its arena
 // (admission by memory: requests with fewer bins take fewer bytes), launches the set when the
 // next request does not fit, when its oldest request has waited max_wait_ms or when no other set
-// runs: the requests' inputs go into the arena in the layout of the shape, the graph of the
+// runs (P in pinned memory is copied to its place while the set still forms): the requests' inputs go into the arena in the layout of the shape, the graph of the
 // smallest captured batch that holds them is replayed, C comes back to pinned host memory and
 // an event marks completion.  Sets launched while others run overlap on the device.
 #include <hip/hip_runtime.h>
@@ -37,6 +37,7 @@ struct Req {
     blast_request r{};
     std::vector<int32_t> ell_idx;
     Clock::time_point t_submit;
+    bool p_sent = false;  // P's copy into its place in the forming set's arena is on the set's stream
 };
 
 struct Done {
@@ -59,6 +60,7 @@ struct Set {
     hipStream_t stream = nullptr;
     unsigned char *arena = nullptr;
     double *C_host = nullptr;  // pinned
+    double *K1_host = nullptr; // pinned: K_chi of a launch's requests
     std::vector<Graph> graphs;
     hipEvent_t done = nullptr;
     std::vector<Req> slots;
@@ -162,6 +164,32 @@ blast_cl_args launch_args(blast_server *S, Set &st, int batch, int G) {
     return a;
 }
 
+// Whether a host pointer is pinned memory that a copy can be enqueued from without waiting
+bool pinned(const void *p) {
+    hipPointerAttribute_t at{};
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeHost;
+}
+
+// Sends the P of a forming set's requests ahead of their launch: P starts the arena in every layout, so its
+// places do not depend on the launch's shape, and the copies (most of a request's bytes) run under the set
+// in flight and the wait for more requests.  Only from pinned memory, whose copies enqueue at once (the
+// caller holds the server's lock); others go with the launch.
+hipError_t send_ahead(blast_server *S, Set &st) {
+    for (size_t k = 0; k < st.slots.size(); ++k) {
+        Req &q = st.slots[k];
+        if (q.p_sent || !pinned(q.r.P)) continue;
+        const hipError_t e =
+            hipMemcpyAsync(st.arena + k * S->P_slot, q.r.P, S->P_slot, hipMemcpyHostToDevice, st.stream);
+        if (e != hipSuccess) return e;
+        q.p_sent = true;
+    }
+    return hipSuccess;
+}
+
 hipError_t launch_set(blast_server *S, Set &st) {
     const int n = (int)st.slots.size();
     const blast_plan *p = S->plan;
@@ -176,22 +204,28 @@ hipError_t launch_set(blast_server *S, Set &st) {
     const Lay L = lay_of(S, b, G);
     const int nb = G + S->d.max_s;
     hipError_t e = hipSuccess;
-    for (int k = 0; k < n && e == hipSuccess; ++k) {
+    // K_chi of all requests is put together in pinned memory and goes in one copy (a small copy costs the engine
+    // as much as a hundred KB); clustering bins at 0..n_g-1, shear bins at G..G+n_s-1, the others zero
+    double *K1h = st.K1_host, *K2 = (double *)(st.arena + L.K2);
+    std::memset(K1h, 0, sizeof(double) * n * nb * p->n_chi);
+    bool gaps = false;
+    for (int k = 0; k < n; ++k) {
         const blast_request &r = st.slots[k].r;
-        e = hipMemcpyAsync(st.arena + L.P + (size_t)k * S->P_slot, r.P, S->P_slot, hipMemcpyHostToDevice, st.stream);
-        double *K1 = (double *)(st.arena + L.K1) + (size_t)k * nb * p->n_chi;
-        double *K2 = (double *)(st.arena + L.K2) + (size_t)k * nb * p->NP;
-        if (e == hipSuccess) e = hipMemsetAsync(K1, 0, sizeof(double) * nb * p->n_chi, st.stream);
-        if (e == hipSuccess) e = hipMemsetAsync(K2, 0, sizeof(double) * nb * p->NP, st.stream);
-        // clustering bins at 0..n_g-1, shear bins at G..G+n_s-1
-        if (e == hipSuccess && r.n_g)
-            e = hipMemcpyAsync(K1, r.K_chi, sizeof(double) * r.n_g * p->n_chi, hipMemcpyHostToDevice, st.stream);
-        if (e == hipSuccess && r.n_s)
-            e = hipMemcpyAsync(K1 + (size_t)G * p->n_chi, r.K_chi + (size_t)r.n_g * p->n_chi,
-                               sizeof(double) * r.n_s * p->n_chi, hipMemcpyHostToDevice, st.stream);
-        if (e == hipSuccess && r.n_g)
-            e = hipMemcpyAsync(K2, r.K_chi2, sizeof(double) * r.n_g * p->NP, hipMemcpyHostToDevice, st.stream);
-        if (e == hipSuccess && r.n_s)
+        double *K1 = K1h + (size_t)k * nb * p->n_chi;
+        std::memcpy(K1, r.K_chi, sizeof(double) * r.n_g * p->n_chi);
+        std::memcpy(K1 + (size_t)G * p->n_chi, r.K_chi + (size_t)r.n_g * p->n_chi, sizeof(double) * r.n_s * p->n_chi);
+        gaps = gaps || r.n_g < G || r.n_s < S->d.max_s;
+    }
+    e = hipMemcpyAsync(st.arena + L.K1, K1h, sizeof(double) * n * nb * p->n_chi, hipMemcpyHostToDevice, st.stream);
+    if (e == hipSuccess && gaps) e = hipMemsetAsync(K2, 0, sizeof(double) * n * nb * p->NP, st.stream);
+    for (int k = 0; k < n && e == hipSuccess; ++k, K2 += (size_t)nb * p->NP) {
+        const blast_request &r = st.slots[k].r;
+        if (!st.slots[k].p_sent)
+            e = hipMemcpyAsync(st.arena + L.P + (size_t)k * S->P_slot, r.P, S->P_slot, hipMemcpyHostToDevice, st.stream);
+        const int n1 = r.n_g == G ? r.n_g + r.n_s : r.n_g;  // without a gap both kinds are one piece
+        if (e == hipSuccess && n1)
+            e = hipMemcpyAsync(K2, r.K_chi2, sizeof(double) * n1 * p->NP, hipMemcpyHostToDevice, st.stream);
+        if (e == hipSuccess && n1 < r.n_g + r.n_s)
             e = hipMemcpyAsync(K2 + (size_t)G * p->NP, r.K_chi2 + (size_t)r.n_g * p->NP,
                                sizeof(double) * r.n_s * p->NP, hipMemcpyHostToDevice, st.stream);
     }
@@ -282,6 +316,7 @@ void scheduler(blast_server *S) {
                 S->queue.pop_front();
             }
             if (S->forming >= 0) {
+                (void)hipStreamSynchronize(S->sets[S->forming].stream);  // no copy may outlive its request
                 for (const Req &q : S->sets[S->forming].slots) finish(S, q, S->fatal, now);
                 S->sets[S->forming].slots.clear();
                 S->forming = -1;
@@ -316,7 +351,12 @@ void scheduler(blast_server *S) {
             const bool waited =
                 !st.slots.empty() && std::chrono::duration<double, std::milli>(Clock::now() - st.slots[0].t_submit)
                                              .count() >= S->d.max_wait_ms;
-            if (!st.slots.empty() && (full || running == 0 || waited || S->stop)) {
+            const bool go = !st.slots.empty() && (full || running == 0 || waited || S->stop);
+            if (!go && !st.slots.empty() && S->fatal == BLAST_OK && send_ahead(S, st) != hipSuccess) {
+                S->fatal = BLAST_E_HIP;
+                continue;
+            }
+            if (go) {
                 S->forming = -1;
                 st.in_flight = true;
                 S->launches++;
@@ -349,6 +389,7 @@ void free_sets(blast_server *S) {
         }
         if (st.arena) (void)hipFree(st.arena);
         if (st.C_host) (void)hipHostFree(st.C_host);
+        if (st.K1_host) (void)hipHostFree(st.K1_host);
         if (st.done) (void)hipEventDestroy(st.done);
         if (st.stream) (void)hipStreamDestroy(st.stream);
     }
@@ -405,6 +446,9 @@ extern "C" blast_status blast_server_create(blast_plan *plan, const blast_server
         if (e == hipSuccess) e = hipEventCreateWithFlags(&st.done, hipEventDisableTiming);
         if (e == hipSuccess) e = hipMalloc((void **)&st.arena, S->set_bytes);
         if (e == hipSuccess) e = hipHostMalloc((void **)&st.C_host, c_host, hipHostMallocDefault);
+        if (e == hipSuccess)
+            e = hipHostMalloc((void **)&st.K1_host, sizeof(double) * d->batch * (d->max_g + d->max_s) * plan->n_chi,
+                              hipHostMallocDefault);
         if (e == hipSuccess) e = hipMemset(st.arena, 0, S->set_bytes);
     }
     blast_status bst = BLAST_OK;
@@ -538,8 +582,12 @@ extern "C" blast_status blast_server_cancel(blast_server *S, uint64_t ticket) {
         Set &st = S->sets[S->forming];
         for (auto it = st.slots.begin(); it != st.slots.end(); ++it)
             if (it->id == ticket) {
+                // P copies on their way end before their requests can; the requests behind this one move up a
+                // place and are sent again
+                if (std::any_of(st.slots.begin(), st.slots.end(), [](const Req &q) { return q.p_sent; }))
+                    (void)hipStreamSynchronize(st.stream);
                 finish(S, *it, BLAST_E_CANCELLED, now);
-                st.slots.erase(it);
+                for (auto b = st.slots.erase(it); b != st.slots.end(); ++b) b->p_sent = false;
                 st.G = 0;
                 for (const Req &q : st.slots) st.G = std::max(st.G, bucket_of(S, q.r.n_g));
                 S->cancelled++;
