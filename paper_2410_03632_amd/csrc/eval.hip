@@ -2631,9 +2631,20 @@ __global__ __launch_bounds__(256) void adj_dy_mfma_kernel(const double *__restri
     const int nca = (n_chi + 15) / 16 * 16;
     for (int i = threadIdx.x; i < kAdjRG * NB * NB; i += blockDim.x) Sd[i] = 0.0;
     const double *Kb = Kchi + (size_t)beta * nbins * n_chi;
-    for (int i = threadIdx.x; i < nca * NB; i += blockDim.x) {
-        const int a = i / NB, l = i % NB;
-        KtT[(size_t)a * KS + l] = (a < n_chi && l < nbins) ? (float)(wchi[a] * chi[a] * Kb[(size_t)l * n_chi + a]) : 0.f;
+    // consecutive lanes take consecutive chi nodes of a bin (whole lines of K_chi), four loads in flight
+    for (int a = threadIdx.x & 63; a < nca; a += 64) {
+        const int ac = min(a, n_chi - 1);
+        const double f = wchi[ac] * chi[ac];
+        for (int l0 = threadIdx.x >> 6; l0 < NB; l0 += 16) {
+            double kv[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) kv[u] = Kb[(size_t)min(l0 + 4 * u, nbins - 1) * n_chi + ac];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int l = l0 + 4 * u;
+                KtT[(size_t)a * KS + l] = (a < n_chi && l < nbins) ? (float)(f * kv[u]) : 0.f;
+            }
+        }
     }
     __syncthreads();
     for (int r = 0; r < kAdjRG; ++r) {
@@ -2877,10 +2888,11 @@ __global__ __launch_bounds__(256) void adj_w_kernel(const T *__restrict__ dY, co
 // takes bins 4 lk + s % 4 + 16 (s / 4) from lane group lk, so a lane reads its row's bins as
 // 16-byte pieces; for dK2, MFMA e of a 16-row chunk takes row 16 c + 4 lk + e, so a lane reads w
 // of its node and dY^T of its bin as 16-byte pieces.  Kh and dY^T (rows past `rows` zero) sit in
-// LDS; w is read from global memory, a chunk of 16-row steps at a time.  Wave v makes the dw tiles
-// v, v + 4, ... and the dK2 node tiles v, v + 4.
+// LDS; w is read from global memory, a chunk of 16-row steps at a time.  The W waves make the
+// dw tiles v, v + W, ... and the dK2 node tiles v, v + W (one wave per node tile where there are 4 to 8 of
+// them, so that none waits for a second one).
 template <int NB>
-__global__ __launch_bounds__(256) void adj_w_mfma_kernel(const float *__restrict__ dY, const float *__restrict__ w,
+__global__ __launch_bounds__(512) void adj_w_mfma_kernel(const float *__restrict__ dY, const float *__restrict__ w,
                                                          const double *__restrict__ Kchi2,
                                                          const double *__restrict__ wR, int batch, int NP, int nR,
                                                          int n_chi, int rows, int rows_pad, int nbins,
@@ -2903,14 +2915,14 @@ __global__ __launch_bounds__(256) void adj_w_mfma_kernel(const float *__restrict
         dYt[(size_t)m * ds + row] = row < rows ? dya[(size_t)row * n_chi * NB + m] : 0.f;
     }
     __syncthreads();
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, W = blockDim.x >> 6;
     const int lr = lane & 15, lk = lane >> 4;
     const size_t base = ((size_t)beta * NP + (size_t)a * nR) * rows_pad;  // w, dw of node b: + b * rows_pad
     const int RTn = rows_pad / 16;
     constexpr int NQ = NB / 16;  // 16-bin groups
     // dw (the A operand from dY^T in LDS: lanes of consecutive rows read consecutive words); staging
     // a node tile's rows in LDS for contiguous stores measured slower (two barriers per tile)
-    for (int tile = wv; tile < RTn * nRt; tile += 4) {
+    for (int tile = wv; tile < RTn * nRt; tile += W) {
         const int rt = tile % RTn, bt = tile / RTn;
         const int row = 16 * rt + lr, b = 16 * bt + lr;
         f4 acc = f4{0, 0, 0, 0};
@@ -2929,7 +2941,7 @@ __global__ __launch_bounds__(256) void adj_w_mfma_kernel(const float *__restrict
     }
     // dK2: node tiles wv, wv + 4, ...; lane (node 16 bt + lr) reads w of that node
     if (dK2) {
-        for (int bt = wv; bt < nRt; bt += 4) {
+        for (int bt = wv; bt < nRt; bt += W) {
             const int b = min(16 * bt + lr, nR - 1);
             const float *wr = w + base + (size_t)b * rows_pad;
             f4 acc[NQ];
@@ -4184,7 +4196,8 @@ blast_status backward(blast_plan *p, const blast_cl_args *a, const double *dC, v
         const dim3 gw = chi_cosmology_grid(p->n_chi, a->batch);                                                   \
         if constexpr (std::is_same<T, float>::value) {                                                           \
             const size_t shw = ((size_t)((p->n_R + 15) / 16 * 16) * NB + (size_t)NB * (p->rows_pad + 4)) * 4;    \
-            hipLaunchKernelGGL((adj_w_mfma_kernel<NB>), gw, dim3(256), shw, s, (const float *)dY,               \
+            const int nrt = (p->n_R + 15) / 16, wav = nrt >= 4 && nrt <= 8 ? nrt : 4;                             \
+            hipLaunchKernelGGL((adj_w_mfma_kernel<NB>), gw, dim3(64 * wav), shw, s, (const float *)dY,               \
                                (const float *)w, a->K_chi2, p->d_wR, a->batch, p->NP, p->n_R, p->n_chi, p->rows, \
                                p->rows_pad, x.nbins, (float *)dw, dK_chi2);                                     \
         } else {                                                                                                  \
