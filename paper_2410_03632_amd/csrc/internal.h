@@ -157,6 +157,7 @@ struct StreamCall {
     int batch, nbins;
     RowTiles tiles;
     int nsplit;         // ranges of R nodes summed apart: Y of range s at Y + s * ysplit
+    int node_waves;     // waves (1; FP64: 1 or 2) that share a row tile, each with every other R node
     int ybs;            // bins per Y row
     size_t ysplit;
     void *Y, *w_out;    // w_out nullable

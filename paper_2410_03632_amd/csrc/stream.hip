@@ -6,14 +6,14 @@
 // At these batches the basis is all the traffic (7.25 GB in FP64 at full 3x2pt against 25 MB of P per
 // cosmology) and one 16-column MFMA tile holds every cosmology, so the work is to keep reads of the
 // basis in flight.  A wave owns one 16-row tile of one chi_a and walks the R nodes with a ring of
-// 16-byte loads in registers; waves of a work-group share only the c rows (LDS, double buffered,
+// 16-byte loads in registers (or half of them, next to a second wave); waves of a work-group share only the c rows (LDS, double buffered,
 // loaded two nodes ahead) and the kernel weights (LDS, a chunk of nodes at a time), with one barrier
 // per node that waits for no load of the basis.
 //
 // Measured (one MI355X, reads alone reach 6.2 TB/s): full 3x2pt in FP64, batch 1, 1.20 ms for 7.28 GB
 // (6.0 TB/s; the contraction with w in memory and its R-quadrature took 1.47 + 0.06), in FP32, batch 8,
-// 0.60 ms for 3.75 GB (6.2 TB/s; 0.73 + 0.12 before); 64 x 32 points of 60 rows in FP64, batch 1, 20 us
-// for 64 MB (45 + 22 before), where the chain of first loads counts, not the rate.
+// 0.60 ms for 3.75 GB (6.2 TB/s; 0.73 + 0.12 before); 64 x 32 points of 60 rows in FP64, batch 1, 19 us
+// for 64 MB (45 + 22 before), where the chain of loads, one node after the other, counts and not the rate.
 //
 // BT columns of the MFMA tile are cosmologies (4, 8 or 16); the 16 / BT copies of each cosmology's w
 // that the tile then holds take a share of the bins each, so a lane keeps Y for 4 rows x NBL bins.
@@ -32,7 +32,7 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t U4 __attribute__((ext_vector_type(4)));
 typedef double d2v __attribute__((ext_vector_type(2)));
 
-constexpr int kStreamWaves = 4;  // row tiles (waves) per work-group
+constexpr int kStreamWaves = 4;  // waves per work-group
 
 // R nodes whose kernel weights sit in LDS together
 template <typename T, int BT, int NBL>
@@ -50,23 +50,28 @@ __device__ inline void lds_barrier() {
 // NC: blocks of 32 columns (nc_pad / 32); BT cosmologies per tile; NBL bins per lane; NPU: nodes held by
 // the ring.
 // TWO: two accumulator chains, K slices 0, 2 and 1, 3 of every four, as contract_quad_kernel<FP32> sums them.
-template <typename T, int NC, int BT, int NBL, int NPU, bool TWO>
-__global__ __launch_bounds__(64 * kStreamWaves, 2) void stream_kernel(
+// SW waves share a row tile: each takes every SW-th R node of the range, their Y are added through LDS at the
+// end (half as many steps where the grid leaves SIMDs idle; 2 waves per tile, FP64: 75 x 29 points of 69 rows,
+// batch 3 with 20 bins, 53 -> 36 us).
+template <typename T, int NC, int BT, int NBL, int NPU, bool TWO, int SW>
+__global__ __launch_bounds__(64 * kStreamWaves, SW > 1 && NBL == 16 ? 1 : 2) void stream_kernel(
     const T *__restrict__ basis, const T *__restrict__ c, int cld, const double *__restrict__ Kchi2,
     const double *__restrict__ wR, int batch, int nbins, int n_chi, int n_R, int rows_pad, RowTiles tiles, int nct,
     int nsplit, int units, int ybs, size_t ysplit, T *__restrict__ Y, T *__restrict__ w_out) {
     constexpr bool F64 = sizeof(T) == 8;
-    constexpr int W = kStreamWaves, VEC = 16 / (int)sizeof(T), L = 8 / VEC;  // loads per block of 32 columns
+    constexpr int W = kStreamWaves, TW = W / SW, VEC = 16 / (int)sizeof(T), L = 8 / VEC;  // loads per block of 32 columns
     constexpr int ncp = 32 * NC, CST = ncp + VEC, GPR = ncp / VEC;
     constexpr int NBT = NBL * 16 / BT, KST = NBT + VEC, CB = stream_chunk<T, BT, NBL>();
-    constexpr int CPT = (BT * GPR + 64 * W - 1) / (64 * W);  // 16-byte pieces of c per thread and node
-    __shared__ __align__(16) T Cs[2][BT * CST];
+    constexpr int CPT = (SW * BT * GPR + 64 * W - 1) / (64 * W);  // 16-byte pieces of c per thread and step
+    // (the c rows' place also takes the Y of one row that waves of a tile add up)
+    constexpr int CSZ = SW * BT * CST, RSZ = SW > 1 ? (W - TW) * 64 * NBL : 0;
+    __shared__ __align__(16) T Cs[2 * CSZ > RSZ ? 2 * CSZ : RSZ];
     __shared__ __align__(16) T Ks[CB * BT * KST];
 
     const int per = (units + 7) / 8;
     const int unit = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
     if (unit >= units) return;  // uniform over the work-group
-    const int groups = (tiles.n + W - 1) / W;
+    const int groups = (tiles.n + TW - 1) / TW;
     // the cosmology tiles of a row group next to each other (they read the same basis tiles), then the
     // row groups of a chi node (they read the same c rows)
     const int ct = unit % nct, grp = (unit / nct) % groups;
@@ -76,8 +81,9 @@ __global__ __launch_bounds__(64 * kStreamWaves, 2) void stream_kernel(
     const int lr = lane & 15, lk = lane >> 4;
     // waves past the last tile repeat it and store nothing: a wave that left the loop's loads out would
     // make the compiler wait for every load in flight where the two paths meet
-    const bool active = grp * W + w < tiles.n;
-    const int rt = tiles.tile(__builtin_amdgcn_readfirstlane(min(grp * W + w, tiles.n - 1)));
+    const int wt = grp * TW + w % TW, h = w / TW;  // tile, first node of the wave
+    const bool active = wt < tiles.n;
+    const int rt = tiles.tile(__builtin_amdgcn_readfirstlane(min(wt, tiles.n - 1)));
     const int col = lr % BT, beta = ct * BT + col, bin0 = (lr / BT) * NBL;
     const int nb = min(BT, batch - ct * BT);
     const size_t NP = (size_t)n_chi * n_R;
@@ -104,23 +110,25 @@ __global__ __launch_bounds__(64 * kStreamWaves, 2) void stream_kernel(
     // c rows: thread's pieces of node b (rows past the batch and pieces past cld repeat valid ones: the
     // columns they feed are not stored, the basis columns they meet are zero)
     const T *pc[CPT];
-    int oc[CPT];
+    int oc[CPT], hc[CPT];
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
-        const int q = min((int)threadIdx.x + i * 64 * W, BT * GPR - 1);
+        const int q = min((int)threadIdx.x + i * 64 * W, SW * BT * GPR - 1);
         const int r = q / GPR, v = q % GPR;
-        pc[i] = c + ((size_t)(ct * BT + min(r, nb - 1)) * NP + (size_t)a * n_R) * cld + min(v, cld / VEC - 1) * VEC;
+        hc[i] = r / BT;
+        pc[i] = c + ((size_t)(ct * BT + min(r % BT, nb - 1)) * NP + (size_t)a * n_R) * cld + min(v, cld / VEC - 1) * VEC;
         oc[i] = r * CST + v * VEC;
     }
     U4 cr[CPT];
     auto load_c = [&](int b) {
 #pragma unroll
-        for (int i = 0; i < CPT; ++i) cr[i] = *(const U4 *)(pc[i] + (size_t)min(b, b1 - 1) * cld);
+        for (int i = 0; i < CPT; ++i) cr[i] = *(const U4 *)(pc[i] + (size_t)min(b + hc[i], b1 - 1) * cld);
     };
     auto store_c = [&](int buf) {
 #pragma unroll
         for (int i = 0; i < CPT; ++i)
-            if (CPT * 64 * W == BT * GPR || (int)threadIdx.x + i * 64 * W < BT * GPR) *(U4 *)(&Cs[buf][oc[i]]) = cr[i];
+            if (CPT * 64 * W == SW * BT * GPR || (int)threadIdx.x + i * 64 * W < SW * BT * GPR)
+                *(U4 *)(&Cs[buf * CSZ + oc[i]]) = cr[i];
     };
 
     T y[4][NBL];
@@ -159,20 +167,20 @@ __global__ __launch_bounds__(64 * kStreamWaves, 2) void stream_kernel(
     load_c(b0);
     stage_weights(b0, min(CB, b1 - b0));  // ahead of the ring, whose loads they would wait for
     store_c(0);
-    load_c(b0 + 1);
+    load_c(b0 + SW);
 #pragma unroll
     for (int nu = 0; nu < NPU; ++nu)
 #pragma unroll
-        for (int j = 0; j < NC; ++j) load_A(nu, j, b0 + nu);
+        for (int j = 0; j < NC; ++j) load_A(nu, j, b0 + nu * SW + h);
 
-    auto node = [&](auto nuc, int b) {
+    auto node = [&](auto nuc, int bs) {  // nodes bs .. bs + SW - 1, one per wave of a tile
         constexpr int nu = decltype(nuc)::value;
-        const int i = b - b0;
-        lds_barrier();  // c(b) and the weights are in LDS; node b - 1's readers are done with the other buffer
+        const int i = (bs - b0) / SW, b = bs + h;
+        lds_barrier();  // c(b) and the weights are in LDS; the last step's readers are done with the other buffer
         store_c((i + 1) & 1);
-        load_c(b + 2);
+        load_c(bs + 2 * SW);
         __builtin_amdgcn_sched_barrier(0);
-        const T *cs = &Cs[i & 1][col * CST + lk * VEC];
+        const T *cs = &Cs[(i & 1) * CSZ + (h * BT + col) * CST + lk * VEC];
         using Acc = typename std::conditional<F64, d4, f4>::type;
         Acc acc = Acc{0, 0, 0, 0}, acc2 = Acc{0, 0, 0, 0};
 #pragma unroll
@@ -195,12 +203,16 @@ __global__ __launch_bounds__(64 * kStreamWaves, 2) void stream_kernel(
                     }
                 }
             }
-            load_A(nu, j, b + NPU);
+            load_A(nu, j, b + NPU * SW);
             __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (TWO) acc = acc + acc2;
+        const bool in = SW == 1 || b < b1;  // (uniform) past the range: the last node again, which adds nothing
+        if constexpr (SW > 1)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] = in ? acc[r] : (T)0;
         // a lane holds w of rows 4 lk + r of the tile for its cosmology
-        if (w_out && active && lr < BT && beta < batch) {
+        if (w_out && active && in && lr < BT && beta < batch) {
             T *wo = w_out + ((size_t)beta * NP + (size_t)a * n_R + b) * rows_pad + 16 * rt + 4 * lk;
             if constexpr (F64) {
                 *(double2 *)wo = make_double2(acc[0], acc[1]);
@@ -209,7 +221,7 @@ __global__ __launch_bounds__(64 * kStreamWaves, 2) void stream_kernel(
                 *(float4 *)wo = make_float4(acc[0], acc[1], acc[2], acc[3]);
             }
         }
-        const T *ks = &Ks[((i % CB) * BT + col) * KST + bin0];
+        const T *ks = &Ks[(((b - b0) % CB) * BT + col) * KST + bin0];
 #pragma unroll
         for (int q0 = 0; q0 < NBL; q0 += VEC) {
             const U4 kk = *(const U4 *)(ks + q0);
@@ -220,26 +232,44 @@ __global__ __launch_bounds__(64 * kStreamWaves, 2) void stream_kernel(
                 for (int r = 0; r < 4; ++r) y[r][q0 + q] = fma(acc[r], k[q], y[r][q0 + q]);
         }
     };
-    static_assert(CB % NPU == 0, "whole rings per weights chunk");
+    static_assert(CB % (NPU * SW) == 0, "whole rings per weights chunk");
     for (int bc = b0; bc < b1; bc += CB) {
         const int be = min(bc + CB, b1);
         if (bc > b0) {
             lds_barrier();  // the previous chunk's readers are done
             stage_weights(bc, be - bc);
         }
-        int b = bc;  // whole rings, then the last nodes of the range
-        for (; b + NPU <= be; b += NPU) {
+        int b = bc;  // whole rings, then the last steps of the range
+        for (; b + (NPU - 1) * SW < be; b += NPU * SW) {
             node(std::integral_constant<int, 0>(), b);
-            if constexpr (NPU > 1) node(std::integral_constant<int, 1>(), b + 1);
-            if constexpr (NPU > 2) node(std::integral_constant<int, 2>(), b + 2);
-            if constexpr (NPU > 3) node(std::integral_constant<int, 3>(), b + 3);
+            if constexpr (NPU > 1) node(std::integral_constant<int, 1>(), b + SW);
+            if constexpr (NPU > 2) node(std::integral_constant<int, 2>(), b + 2 * SW);
+            if constexpr (NPU > 3) node(std::integral_constant<int, 3>(), b + 3 * SW);
         }
         if constexpr (NPU > 1)
             if (b < be) node(std::integral_constant<int, 0>(), b);
         if constexpr (NPU > 2) {
-            if (b + 1 < be) node(std::integral_constant<int, 1>(), b + 1);
-            if (b + 2 < be) node(std::integral_constant<int, 2>(), b + 2);
+            if (b + SW < be) node(std::integral_constant<int, 1>(), b + SW);
+            if (b + 2 * SW < be) node(std::integral_constant<int, 2>(), b + 2 * SW);
         }
+    }
+    if constexpr (SW > 1) {
+        // the tile's waves add up in the order of their first nodes, one row at a time
+        T *red = Cs + ((size_t)(w % TW) * 64 + lane) * NBL;  // wave h of tile t at + ((h - 1) * TW + t) * 64 * NBL
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            lds_barrier();  // the readers of what lay here are done
+            if (h > 0)
+#pragma unroll
+                for (int q = 0; q < NBL; ++q) red[(size_t)(h - 1) * TW * 64 * NBL + q] = y[r][q];
+            lds_barrier();
+            if (h == 0)
+#pragma unroll
+                for (int o = 0; o < SW - 1; ++o)
+#pragma unroll
+                    for (int q = 0; q < NBL; ++q) y[r][q] += red[(size_t)o * TW * 64 * NBL + q];
+        }
+        if (h > 0) return;
     }
     if (!active || beta >= batch) return;
 #pragma unroll
@@ -261,15 +291,21 @@ __global__ __launch_bounds__(64 * kStreamWaves, 2) void stream_kernel(
 template <typename T>
 void launch(const StreamCall &k, hipStream_t s) {
     const blast_plan *p = k.plan;
-    auto go2 = [&](auto nct_, auto btt, auto nblt, auto nput, auto twot) {
+    auto go3 = [&](auto nct_, auto btt, auto nblt, auto nput, auto twot, auto swt) {
         constexpr int NC = decltype(nct_)::value, BT = decltype(btt)::value, NBL = decltype(nblt)::value;
-        constexpr int NPU = decltype(nput)::value;
-        const int nct = (k.batch + BT - 1) / BT, groups = (k.tiles.n + kStreamWaves - 1) / kStreamWaves;
+        constexpr int NPU = decltype(nput)::value, SW = decltype(swt)::value, TW = kStreamWaves / SW;
+        const int nct = (k.batch + BT - 1) / BT, groups = (k.tiles.n + TW - 1) / TW;
         const int units = p->n_chi * k.nsplit * groups * nct;
-        hipLaunchKernelGGL((stream_kernel<T, NC, BT, NBL, NPU, decltype(twot)::value>), dim3((unsigned)((units + 7) / 8 * 8)),
+        hipLaunchKernelGGL((stream_kernel<T, NC, BT, NBL, NPU, decltype(twot)::value, SW>), dim3((unsigned)((units + 7) / 8 * 8)),
                            dim3(64 * kStreamWaves), 0, s, (const T *)k.basis, (const T *)k.c, k.cld, k.K_chi2, p->d_wR,
                            k.batch, k.nbins, p->n_chi, p->n_R, p->rows_pad, k.tiles, nct, k.nsplit, units, k.ybs,
                            k.ysplit, (T *)k.Y, (T *)k.w_out);
+    };
+    auto go2 = [&](auto nct_, auto btt, auto nblt, auto nput, auto twot) {
+        using std::integral_constant;
+        if constexpr (sizeof(T) == 8)
+            if (k.node_waves == 2) return go3(nct_, btt, nblt, nput, twot, integral_constant<int, 2>());
+        go3(nct_, btt, nblt, nput, twot, integral_constant<int, 1>());
     };
     // (only batches past the fused kernels' smallest take their two chains: the widest tiles)
     auto go = [&](auto nct_, auto btt, auto nblt, auto nput) {
