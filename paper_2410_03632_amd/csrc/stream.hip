@@ -32,7 +32,6 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t U4 __attribute__((ext_vector_type(4)));
 typedef double d2v __attribute__((ext_vector_type(2)));
 
-constexpr int kStreamWaves = 4;  // waves per work-group
 
 // R nodes whose kernel weights sit in LDS together
 template <typename T, int BT, int NBL>
@@ -53,13 +52,13 @@ __device__ inline void lds_barrier() {
 // SW waves share a row tile: each takes every SW-th R node of the range, their Y are added through LDS at the
 // end (half as many steps where the grid leaves SIMDs idle; 2 waves per tile, FP64: 75 x 29 points of 69 rows,
 // batch 3 with 20 bins, 53 -> 36 us).
-template <typename T, int NC, int BT, int NBL, int NPU, bool TWO, int SW>
-__global__ __launch_bounds__(64 * kStreamWaves, SW > 1 && NBL == 16 ? 1 : 2) void stream_kernel(
+template <typename T, int NC, int BT, int NBL, int NPU, bool TWO, int SW, int W>
+__global__ __launch_bounds__(64 * W, SW > 1 && NBL == 16 ? 1 : 2) void stream_kernel(
     const T *__restrict__ basis, const T *__restrict__ c, int cld, const double *__restrict__ Kchi2,
     const double *__restrict__ wR, int batch, int nbins, int n_chi, int n_R, int rows_pad, RowTiles tiles, int nct,
     int nsplit, int units, int ybs, size_t ysplit, T *__restrict__ Y, T *__restrict__ w_out) {
     constexpr bool F64 = sizeof(T) == 8;
-    constexpr int W = kStreamWaves, TW = W / SW, VEC = 16 / (int)sizeof(T), L = 8 / VEC;  // loads per block of 32 columns
+    constexpr int TW = W / SW, VEC = 16 / (int)sizeof(T), L = 8 / VEC;  // loads per block of 32 columns
     constexpr int ncp = 32 * NC, CST = ncp + VEC, GPR = ncp / VEC;
     constexpr int NBT = NBL * 16 / BT, KST = NBT + VEC, CB = stream_chunk<T, BT, NBL>();
     constexpr int CPT = (SW * BT * GPR + 64 * W - 1) / (64 * W);  // 16-byte pieces of c per thread and step
@@ -140,14 +139,13 @@ __global__ __launch_bounds__(64 * kStreamWaves, SW > 1 && NBL == 16 ? 1 : 2) voi
     // weights of nodes b .. b + nn - 1 into LDS
     auto stage_weights = [&](int b, int nn) {
         // KU loads in flight per thread (clamped addresses, values masked)
-        constexpr int KPT = CB * BT * NBT / (64 * W), KU = KPT < 8 ? KPT : (F64 && NBL == 16 ? 4 : 8);
-        static_assert(KPT * 64 * W == CB * BT * NBT && KPT % KU == 0, "whole weights per thread");
+        constexpr int KN = CB * BT * NBT, KPT = (KN + 64 * W - 1) / (64 * W), KU = KPT < 8 ? KPT : (F64 && NBL == 16 ? 4 : 8);
 #pragma unroll
-        for (int q0 = 0; q0 < KPT; q0 += KU) {
+        for (int q0 = 0; q0 < KPT; q0 += KU) {  // (past the last weight: the last again, not stored)
             double kv[KU];
 #pragma unroll
             for (int u = 0; u < KU; ++u) {
-                const int q = (int)threadIdx.x + (q0 + u) * 64 * W;
+                const int q = min((int)threadIdx.x + (q0 + u) * 64 * W, KN - 1);
                 const int bb = min(q % CB, nn - 1), bin = min((q / CB) % NBT, nbins - 1), cc = min(q / (CB * NBT), nb - 1);
                 kv[u] = Kchi2[((size_t)(ct * BT + cc) * nbins + bin) * NP + (size_t)a * n_R + b + bb];
             }
@@ -158,6 +156,7 @@ __global__ __launch_bounds__(64 * kStreamWaves, SW > 1 && NBL == 16 ? 1 : 2) voi
 #pragma unroll
             for (int u = 0; u < KU; ++u) {
                 const int q = (int)threadIdx.x + (q0 + u) * 64 * W;
+                if (KN % (64 * W * KU) != 0 && q >= KN) break;
                 const int bb = q % CB, bin = (q / CB) % NBT, cc = q / (CB * NBT);
                 Ks[(bb * BT + cc) * KST + bin] = bb < nn && bin < nbins && cc < nb ? (T)(wv * kv[u]) : (T)0;
             }
@@ -291,15 +290,28 @@ __global__ __launch_bounds__(64 * kStreamWaves, SW > 1 && NBL == 16 ? 1 : 2) voi
 template <typename T>
 void launch(const StreamCall &k, hipStream_t s) {
     const blast_plan *p = k.plan;
-    auto go3 = [&](auto nct_, auto btt, auto nblt, auto nput, auto twot, auto swt) {
+    auto go4 = [&](auto nct_, auto btt, auto nblt, auto nput, auto twot, auto swt, auto wt) {
         constexpr int NC = decltype(nct_)::value, BT = decltype(btt)::value, NBL = decltype(nblt)::value;
-        constexpr int NPU = decltype(nput)::value, SW = decltype(swt)::value, TW = kStreamWaves / SW;
+        constexpr int NPU = decltype(nput)::value, SW = decltype(swt)::value, W = decltype(wt)::value, TW = W / SW;
         const int nct = (k.batch + BT - 1) / BT, groups = (k.tiles.n + TW - 1) / TW;
         const int units = p->n_chi * k.nsplit * groups * nct;
-        hipLaunchKernelGGL((stream_kernel<T, NC, BT, NBL, NPU, decltype(twot)::value, SW>), dim3((unsigned)((units + 7) / 8 * 8)),
-                           dim3(64 * kStreamWaves), 0, s, (const T *)k.basis, (const T *)k.c, k.cld, k.K_chi2, p->d_wR,
+        hipLaunchKernelGGL((stream_kernel<T, NC, BT, NBL, NPU, decltype(twot)::value, SW, W>), dim3((unsigned)((units + 7) / 8 * 8)),
+                           dim3(64 * W), 0, s, (const T *)k.basis, (const T *)k.c, k.cld, k.K_chi2, p->d_wR,
                            k.batch, k.nbins, p->n_chi, p->n_R, p->rows_pad, k.tiles, nct, k.nsplit, units, k.ybs,
                            k.ysplit, (T *)k.Y, (T *)k.w_out);
+    };
+    auto go3 = [&](auto nct_, auto btt, auto nblt, auto nput, auto twot, auto swt) {
+        using std::integral_constant;
+        if constexpr (sizeof(T) == 4) {
+            constexpr int BT = decltype(btt)::value;
+            const int g = p->n_chi * ((k.batch + BT - 1) / BT), w4 = g * ((k.tiles.n + 3) / 4), w6 = g * ((k.tiles.n + 5) / 6);
+            // 6 waves per work-group where that saves the busiest CU a work-group (results unchanged): 75 chi nodes,
+            // 5 row tiles, 37 cosmologies 53.1 -> 46.5 us, 31 cosmologies of 128 nodes 58.7 -> 49.6; from three
+            // work-groups per CU on the same or slower (540 of 12 tiles: 107.0 -> 107.9)
+            if (w4 <= 512 && (w6 + 255) / 256 < (w4 + 255) / 256)
+                return go4(nct_, btt, nblt, nput, twot, swt, integral_constant<int, 6>());
+        }
+        go4(nct_, btt, nblt, nput, twot, swt, integral_constant<int, 4>());
     };
     auto go2 = [&](auto nct_, auto btt, auto nblt, auto nput, auto twot) {
         using std::integral_constant;
