@@ -4020,31 +4020,34 @@ blast_status forward_impl(blast_plan *p, const blast_cl_args *a, hipStream_t s, 
         k.batch = a->batch;
         k.nbins = x.nbins;
         k.tiles = row_tiles(p, a, x, a->w_save || a->y_save);
-        k.node_waves = 1;
+        k.nsplit = k.node_waves = 1;
         const int rtiles = p->rows_pad / 16;
         if (f64 && p->n_chi * rtiles <= 1024) {
             // Grids of at most one wave per SIMD are bound by a work-group's chain of R nodes: they share the
-            // nodes out over ns ranges summed apart (in the scratch that w would take) and over two waves per
-            // row tile (FP64; the FP32 sums keep their order), whichever takes the fewest steps: work-groups on
-            // the same CU take turns (75 x 29 points, 5 row tiles: 225 work-groups of 15 steps 26 us, 300 of 15
-            // 39, 150 of 29 36; 140 chi nodes: 420 of 15 57, 280 of 29 94), a work-group's start and end cost
-            // about 4 steps, a range 2 in the chi-quadrature.  The choice is the plan's alone, so that a
-            // cosmology's result does not depend on the batch, the multipoles or (up to 16) the bins it comes
-            // with.
-            const int most = need_w && !a->y_save ? std::min((p->n_R + x.nbp) / x.nbp, p->n_R / 4) : 1;
+            // nodes out over ns ranges summed apart and over two waves per row tile (FP64; the FP32 sums keep
+            // their order), whichever takes the fewest steps: work-groups on the same CU take turns (75 x 29
+            // points, 5 row tiles: 225 work-groups of 15 steps 26 us, 300 of 15 39, 150 of 29 36; 140 chi nodes:
+            // 420 of 15 57, 280 of 29 94), a work-group's start and end cost about 4 steps, a range 2 in the
+            // chi-quadrature.  The order of the sums follows from the plan alone, so that a streamed result does
+            // not depend on the batch, the multipoles, the bins or the saved arrays a cosmology comes with: where
+            // the scratch that w would take is not there (a call that keeps w) or does not hold the ranges' Y
+            // (more than 16 bins), or where Y itself is kept, the ranges run one after the other into one Y.
+            const int most = std::max(std::min(p->n_R / 16 + 1, p->n_R / 4), 1);
             int ns = 1, best = 1 << 30;
             for (int sw = 1; sw <= 2; ++sw)
-                for (int n = 1; n <= std::max(most, 1); ++n) {
+                for (int n = 1; n <= most; ++n) {
                     const int wgs = p->n_chi * ((rtiles * sw + 3) / 4) * n;
                     const int cost = (wgs + 255) / 256 * ((p->n_R + n * sw - 1) / (n * sw) + 4) + 2 * (n - 1);
                     if (cost < best) best = cost, ns = n, k.node_waves = sw;
                 }
-            if (ns > 1) {
+            k.nsplit = ns;
+            // (w's and Y's place in the scratch are neighbours)
+            k.apart = ns > 1 && need_w && !a->y_save && ns <= (p->n_R + x.nbp) / x.nbp;
+            if (k.apart) {
                 sy = YShape{ns, (size_t)a->batch * p->rows_pad * p->n_chi * x.nbp};
                 Y = ws + L.w;
             }
         }
-        k.nsplit = sy.nsplit;
         k.ybs = x.nbp;
         k.ysplit = sy.ysplit;
         k.Y = Y;

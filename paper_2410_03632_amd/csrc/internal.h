@@ -156,7 +156,9 @@ struct StreamCall {
     const double *K_chi2;
     int batch, nbins;
     RowTiles tiles;
-    int nsplit;         // ranges of R nodes summed apart: Y of range s at Y + s * ysplit
+    int nsplit;         // ranges of R nodes that Y sums, in their order
+    bool apart;         // each range into its own Y, range s at Y + s * ysplit (one launch); else one launch per
+                        // range, each adding to Y (FP64)
     int node_waves;     // waves (1; FP64: 1 or 2) that share a row tile, each with every other R node
     int ybs;            // bins per Y row
     size_t ysplit;

@@ -49,6 +49,8 @@ __device__ inline void lds_barrier() {
 // NC: blocks of 32 columns (nc_pad / 32); BT cosmologies per tile; NBL bins per lane; NPU: nodes held by
 // the ring.
 // TWO: two accumulator chains, K slices 0, 2 and 1, 3 of every four, as contract_quad_kernel<FP32> sums them.
+// The launch sums ranges sp0 .. sp0 + nsp - 1 of the nsplit ranges of R nodes, range sp0 + i at Y + i * ysplit;
+// from sp0 > 0 (FP64) on top of what is there.
 // SW waves share a row tile: each takes every SW-th R node of the range, their Y are added through LDS at the
 // end (half as many steps where the grid leaves SIMDs idle; 2 waves per tile, FP64: 75 x 29 points of 69 rows,
 // batch 3 with 20 bins, 53 -> 36 us).
@@ -56,7 +58,7 @@ template <typename T, int NC, int BT, int NBL, int NPU, bool TWO, int SW, int W>
 __global__ __launch_bounds__(64 * W, SW > 1 && NBL == 16 ? 1 : 2) void stream_kernel(
     const T *__restrict__ basis, const T *__restrict__ c, int cld, const double *__restrict__ Kchi2,
     const double *__restrict__ wR, int batch, int nbins, int n_chi, int n_R, int rows_pad, RowTiles tiles, int nct,
-    int nsplit, int units, int ybs, size_t ysplit, T *__restrict__ Y, T *__restrict__ w_out) {
+    int nsplit, int sp0, int nsp, int units, int ybs, size_t ysplit, T *__restrict__ Y, T *__restrict__ w_out) {
     constexpr bool F64 = sizeof(T) == 8;
     constexpr int TW = W / SW, VEC = 16 / (int)sizeof(T), L = 8 / VEC;  // loads per block of 32 columns
     constexpr int ncp = 32 * NC, CST = ncp + VEC, GPR = ncp / VEC;
@@ -74,7 +76,7 @@ __global__ __launch_bounds__(64 * W, SW > 1 && NBL == 16 ? 1 : 2) void stream_ke
     // the cosmology tiles of a row group next to each other (they read the same basis tiles), then the
     // row groups of a chi node (they read the same c rows)
     const int ct = unit % nct, grp = (unit / nct) % groups;
-    const int sp = (unit / (nct * groups)) % nsplit, a = unit / (nct * groups * nsplit);
+    const int sp = sp0 + (unit / (nct * groups)) % nsp, a = unit / (nct * groups * nsp);
     const int b0 = (int)((long)n_R * sp / nsplit), b1 = (int)((long)n_R * (sp + 1) / nsplit);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int lr = lane & 15, lk = lane >> 4;
@@ -274,7 +276,7 @@ __global__ __launch_bounds__(64 * W, SW > 1 && NBL == 16 ? 1 : 2) void stream_ke
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int row = 16 * rt + 4 * lk + r;
-        T *yp = Y + (size_t)sp * ysplit + (((size_t)beta * rows_pad + row) * n_chi + a) * ybs + bin0;
+        T *yp = Y + (size_t)(sp - sp0) * ysplit + (((size_t)beta * rows_pad + row) * n_chi + a) * ybs + bin0;
 #pragma unroll
         for (int q0 = 0; q0 < NBL; q0 += VEC) {
             if (bin0 + q0 >= ybs) continue;
@@ -282,6 +284,11 @@ __global__ __launch_bounds__(64 * W, SW > 1 && NBL == 16 ? 1 : 2) void stream_ke
             T *op = (T *)&o;
 #pragma unroll
             for (int q = 0; q < VEC; ++q) op[q] = y[r][q0 + q];
+            if constexpr (F64)
+                if (sp0 > 0) {  // ranges one launch after the other: on top of the earlier ones' sum
+                    const U4 old = *(const U4 *)(yp + q0);
+                    o = __builtin_bit_cast(U4, __builtin_bit_cast(d2v, old) + __builtin_bit_cast(d2v, o));
+                }
             *(U4 *)(yp + q0) = o;
         }
     }
@@ -294,11 +301,13 @@ void launch(const StreamCall &k, hipStream_t s) {
         constexpr int NC = decltype(nct_)::value, BT = decltype(btt)::value, NBL = decltype(nblt)::value;
         constexpr int NPU = decltype(nput)::value, SW = decltype(swt)::value, W = decltype(wt)::value, TW = W / SW;
         const int nct = (k.batch + BT - 1) / BT, groups = (k.tiles.n + TW - 1) / TW;
-        const int units = p->n_chi * k.nsplit * groups * nct;
-        hipLaunchKernelGGL((stream_kernel<T, NC, BT, NBL, NPU, decltype(twot)::value, SW, W>), dim3((unsigned)((units + 7) / 8 * 8)),
-                           dim3(64 * W), 0, s, (const T *)k.basis, (const T *)k.c, k.cld, k.K_chi2, p->d_wR,
-                           k.batch, k.nbins, p->n_chi, p->n_R, p->rows_pad, k.tiles, nct, k.nsplit, units, k.ybs,
-                           k.ysplit, (T *)k.Y, (T *)k.w_out);
+        const int nsp = k.apart ? k.nsplit : 1, units = p->n_chi * nsp * groups * nct;
+        for (int sp0 = 0; sp0 < k.nsplit; sp0 += nsp)
+            hipLaunchKernelGGL((stream_kernel<T, NC, BT, NBL, NPU, decltype(twot)::value, SW, W>),
+                               dim3((unsigned)((units + 7) / 8 * 8)), dim3(64 * W), 0, s, (const T *)k.basis,
+                               (const T *)k.c, k.cld, k.K_chi2, p->d_wR, k.batch, k.nbins, p->n_chi, p->n_R,
+                               p->rows_pad, k.tiles, nct, k.nsplit, sp0, nsp, units, k.ybs, k.ysplit, (T *)k.Y,
+                               (T *)k.w_out);
     };
     auto go3 = [&](auto nct_, auto btt, auto nblt, auto nput, auto twot, auto swt) {
         using std::integral_constant;
