@@ -3900,20 +3900,66 @@ void stage_quad_c(blast_plan *p, const blast_cl_args *a, const Ctx &x, const voi
     else by_bins(TypeTag<float>());
 }
 
-// stages 2 + 3 by streaming the basis (stream.hip): FP64 and FP32 below kFusedMinBatch, and from there on
-// where the fused kernels (which then take the call otherwise, and whose FP32 sums the streaming kernel
-// repeats bit for bit) have too few work-groups for the chip.  Counted in the streaming kernel's waves, on
-// grids from 24 x 16 to 128 x 48 points at batches 33-256: FP32 1.06 to 2.1 times the fused kernel's speed up
-// to 2048 waves and 0.75-1.2 times above; FP64, whose fused kernel reuses a basis tile for 64 cosmologies
-// where this one reuses it for 16, 1.26 to 1.8 times up to 768 waves on two row tiles, 0.98-1.12 on four.
+// How a plan's FP64 streaming calls share out the R nodes: ns ranges summed apart, waves per row tile
+struct RSplit {
+    int ns, waves;
+};
+
+// Grids of at most one wave per SIMD are bound by a work-group's chain of R nodes: they share the nodes out over
+// ns ranges summed apart and over two waves per row tile (FP64; the FP32 sums keep their order), whichever takes
+// the fewest steps: work-groups on the same CU take turns (75 x 29 points, 5 row tiles: 225 work-groups of 15
+// steps 26 us, 300 of 15 39, 150 of 29 36; 140 chi nodes: 420 of 15 57, 280 of 29 94), a work-group's start and
+// end cost about 4 steps, a range 2 in the chi-quadrature.  The order of the sums follows from the plan alone, so
+// that a streamed result does not depend on the batch, the multipoles, the bins or the saved arrays a cosmology
+// comes with.
+RSplit r_split(const blast_plan *p, int prec) {
+    RSplit r{1, 1};
+    const int rtiles = p->rows_pad / 16;
+    if (prec != BLAST_FP64 || p->n_chi * rtiles > 1024) return r;
+    const int most = std::max(std::min(p->n_R / 16 + 1, p->n_R / 4), 1);
+    int best = 1 << 30;
+    for (int sw = 1; sw <= 2; ++sw)
+        for (int n = 1; n <= most; ++n) {
+            const int wgs = p->n_chi * ((rtiles * sw + 3) / 4) * n;
+            const int cost = (wgs + 255) / 256 * ((p->n_R + n * sw - 1) / (n * sw) + 4) + 2 * (n - 1);
+            if (cost < best) best = cost, r = RSplit{n, sw};
+        }
+    return r;
+}
+
+// stages 2 + 3 by streaming the basis (stream.hip), FP64 and FP32.
+//
+// Below kFusedMinBatch, in place of the contraction through w (one basis read for all of 32 or 64 cosmologies, the
+// same sums bit for bit): always with one cosmology tile; with more, every further tile reads the basis again,
+// mostly from cache, which on basis points of more than 8 row tiles of more than 64 columns can cost more than w.
+// Measured over grids from 40 x 29 points of 12 row tiles to the full 3x2pt one (256 x 96, 18 row tiles), speed
+// against w's route: one tile 1.1 to 2.5; smaller points 1.0 to 1.9 at any number of tiles; larger ones at two
+// tiles FP32 1.1 to 1.3, FP64 0.95 to 1.23 (full 3x2pt 0.92 to 0.96 while less than a quarter of the second tile
+// is used, from there on 0.99 to 1.13), at three FP32 0.92 to 1.06 up to half of the third, then 1.01 to 1.2,
+// FP64 0.81 to 1.05, at four FP32 0.90 to 1.04, FP64 0.75 to 0.93.  FP64 plans that split the R sums stream in any
+// case, for one order of the sums (40 x 29 points, 12 row tiles: 0.95 to 1.07 at three and four tiles).
+//
+// From there on where the fused kernels (which then take the call otherwise, and whose FP32 sums the streaming
+// kernel repeats bit for bit) have too few work-groups for the chip.  Counted in waves, on grids from 24 x 16 to
+// 128 x 48 points at batches 33-256: FP32 1.06 to 2.1 times the fused kernel's speed up to 2048 waves of 16
+// cosmologies and 0.75-1.2 times above; with 17 to 20 bins, whose tiles hold 8, 1.07 to 2.2 up to 4096 waves and
+// on the larger points 1.1 at 2400, 0.94 at 3840; FP64, whose fused kernel reuses a basis tile for 64 cosmologies
+// where this one reuses it for 16, 1.26 to 1.8 times up to 512 waves and 0.98-1.12 at 768 waves of four row tiles.
 // One row tile leaves three of four waves idle (0.6-1.06).
 bool streams(const blast_plan *p, const Ctx &x, int batch) {
-    if (x.prec != BLAST_FP64 && x.prec != BLAST_FP32) return false;
-    if (batch < kFusedMinBatch) return true;
-    if (x.nbins > (x.prec == BLAST_FP64 ? 16 : 20)) return false;
-    const int RT = p->rows_pad / 16;
-    const long waves = (long)p->n_chi * ((RT + 3) / 4 * 4) * ((batch + 15) / 16);
-    return RT > 1 && waves <= (x.prec == BLAST_FP64 ? 512 : 2048);
+    const bool f64 = x.prec == BLAST_FP64;
+    if (!f64 && x.prec != BLAST_FP32) return false;
+    const int RT = p->rows_pad / 16, BT = stream_tile(batch, x.nbins), tiles = (batch + BT - 1) / BT;
+    const bool large = RT > 8 && p->nc_pad > 64;  // basis points
+    if (batch < kFusedMinBatch) {
+        const RSplit r = r_split(p, x.prec);
+        if (tiles == 1 || !large || r.ns > 1 || r.waves > 1) return true;
+        if (tiles == 2) return !f64 || (size_t)p->rows_pad * p->nc_pad * 8 <= 256 * 1024 || batch >= BT + BT / 4;
+        return tiles == 3 && !f64 && batch > 2 * BT + BT / 2;
+    }
+    if (x.nbins > (f64 ? 16 : 20)) return false;
+    const long waves = (long)p->n_chi * ((RT + 3) / 4 * 4) * tiles;
+    return RT > 1 && waves <= (f64 ? 512 : BT == 16 ? 2048 : large ? 3072 : 4096);
 }
 
 // the 16-row tiles that hold a requested multipole of a requested type
@@ -4020,33 +4066,16 @@ blast_status forward_impl(blast_plan *p, const blast_cl_args *a, hipStream_t s, 
         k.batch = a->batch;
         k.nbins = x.nbins;
         k.tiles = row_tiles(p, a, x, a->w_save || a->y_save);
-        k.nsplit = k.node_waves = 1;
-        const int rtiles = p->rows_pad / 16;
-        if (f64 && p->n_chi * rtiles <= 1024) {
-            // Grids of at most one wave per SIMD are bound by a work-group's chain of R nodes: they share the
-            // nodes out over ns ranges summed apart and over two waves per row tile (FP64; the FP32 sums keep
-            // their order), whichever takes the fewest steps: work-groups on the same CU take turns (75 x 29
-            // points, 5 row tiles: 225 work-groups of 15 steps 26 us, 300 of 15 39, 150 of 29 36; 140 chi nodes:
-            // 420 of 15 57, 280 of 29 94), a work-group's start and end cost about 4 steps, a range 2 in the
-            // chi-quadrature.  The order of the sums follows from the plan alone, so that a streamed result does
-            // not depend on the batch, the multipoles, the bins or the saved arrays a cosmology comes with: where
-            // the scratch that w would take is not there (a call that keeps w) or does not hold the ranges' Y
-            // (more than 16 bins), or where Y itself is kept, the ranges run one after the other into one Y.
-            const int most = std::max(std::min(p->n_R / 16 + 1, p->n_R / 4), 1);
-            int ns = 1, best = 1 << 30;
-            for (int sw = 1; sw <= 2; ++sw)
-                for (int n = 1; n <= most; ++n) {
-                    const int wgs = p->n_chi * ((rtiles * sw + 3) / 4) * n;
-                    const int cost = (wgs + 255) / 256 * ((p->n_R + n * sw - 1) / (n * sw) + 4) + 2 * (n - 1);
-                    if (cost < best) best = cost, ns = n, k.node_waves = sw;
-                }
-            k.nsplit = ns;
-            // (w's and Y's place in the scratch are neighbours)
-            k.apart = ns > 1 && need_w && !a->y_save && ns <= (p->n_R + x.nbp) / x.nbp;
-            if (k.apart) {
-                sy = YShape{ns, (size_t)a->batch * p->rows_pad * p->n_chi * x.nbp};
-                Y = ws + L.w;
-            }
+        const RSplit r = r_split(p, x.prec);
+        k.nsplit = r.ns;
+        k.node_waves = r.waves;
+        // Each range into a Y of its own, in the scratch that w would take and Y's next to it.  Where that is not
+        // there (a call that keeps w) or does not hold them (more than 16 bins), or where Y itself is kept, the
+        // ranges run one after the other into one Y.
+        k.apart = r.ns > 1 && need_w && !a->y_save && r.ns <= (p->n_R + x.nbp) / x.nbp;
+        if (k.apart) {
+            sy = YShape{r.ns, (size_t)a->batch * p->rows_pad * p->n_chi * x.nbp};
+            Y = ws + L.w;
         }
         k.ybs = x.nbp;
         k.ysplit = sy.ysplit;

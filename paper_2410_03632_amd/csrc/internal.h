@@ -148,6 +148,8 @@ struct RowTiles {  // the 16-row tiles of the basis that a call computes, four t
     __host__ __device__ int tile(int i) const { return (int)(t[i >> 2] >> (8 * (i & 3)) & 255u); }
     void add(int v) { t[n >> 2] |= (uint32_t)v << (8 * (n & 3)), ++n; }
 };
+// cosmologies per tile of a streaming call's kernel
+inline int stream_tile(int batch, int nbins) { return batch <= 4 ? 4 : batch <= 8 || nbins > 16 ? 8 : 16; }
 struct StreamCall {
     const blast_plan *plan;
     const void *basis;  // FP64 row-major or FP32 tiled, matching c

@@ -6,9 +6,9 @@
 // At these batches the basis is all the traffic (7.25 GB in FP64 at full 3x2pt against 25 MB of P per
 // cosmology) and one 16-column MFMA tile holds every cosmology, so the work is to keep reads of the
 // basis in flight.  A wave owns one 16-row tile of one chi_a and walks the R nodes with a ring of
-// 16-byte loads in registers (or half of them, next to a second wave); waves of a work-group share only the c rows (LDS, double buffered,
-// loaded two nodes ahead) and the kernel weights (LDS, a chunk of nodes at a time), with one barrier
-// per node that waits for no load of the basis.
+// 16-byte loads in registers (or half of them, next to a second wave); waves of a work-group share only the
+// c rows (LDS, double buffered, loaded two nodes ahead) and the kernel weights (LDS, a chunk of nodes at a
+// time), with one barrier per node that waits for no load of the basis.
 //
 // Measured (one MI355X, reads alone reach 6.2 TB/s): full 3x2pt in FP64, batch 1, 1.20 ms for 7.28 GB
 // (6.0 TB/s; the contraction with w in memory and its R-quadrature took 1.47 + 0.06), in FP32, batch 8,
@@ -48,13 +48,14 @@ __device__ inline void lds_barrier() {
 
 // NC: blocks of 32 columns (nc_pad / 32); BT cosmologies per tile; NBL bins per lane; NPU: nodes held by
 // the ring.
+// ONCE: one cosmology tile, so that a basis tile is read once.
 // TWO: two accumulator chains, K slices 0, 2 and 1, 3 of every four, as contract_quad_kernel<FP32> sums them.
 // The launch sums ranges sp0 .. sp0 + nsp - 1 of the nsplit ranges of R nodes, range sp0 + i at Y + i * ysplit;
 // from sp0 > 0 (FP64) on top of what is there.
 // SW waves share a row tile: each takes every SW-th R node of the range, their Y are added through LDS at the
 // end (half as many steps where the grid leaves SIMDs idle; 2 waves per tile, FP64: 75 x 29 points of 69 rows,
 // batch 3 with 20 bins, 53 -> 36 us).
-template <typename T, int NC, int BT, int NBL, int NPU, bool TWO, int SW, int W>
+template <typename T, int NC, int BT, int NBL, int NPU, bool TWO, bool ONCE, int SW, int W>
 __global__ __launch_bounds__(64 * W, SW > 1 && NBL == 16 ? 1 : 2) void stream_kernel(
     const T *__restrict__ basis, const T *__restrict__ c, int cld, const double *__restrict__ Kchi2,
     const double *__restrict__ wR, int batch, int nbins, int n_chi, int n_R, int rows_pad, RowTiles tiles, int nct,
@@ -101,10 +102,12 @@ __global__ __launch_bounds__(64 * W, SW > 1 && NBL == 16 ? 1 : 2) void stream_ke
         const U4 *q = pa + (size_t)(min(b, b1 - 1) - b0) * nst;
 #pragma unroll
         for (int l = 0; l < L; ++l) {
-            // non-temporal where an instruction takes whole lines (FP32, tiled: 596 us instead of 703 at full
-            // 3x2pt, batch 8); the row-major FP64 loads take half a line each, and the other half must
-            // still be there for the next (1204 us instead of 1380 at batch 1)
-            if constexpr (F64) A[nu][j][l] = q[(j * L + l) * PST];
+            // non-temporal where an instruction takes whole lines that nobody reads again (FP32, tiled, one
+            // cosmology tile: 596 us instead of 703 at full 3x2pt, batch 8); the tiles of a larger batch read them
+            // one soon after the other (batch 17: 938 us instead of 1265), and the row-major FP64 loads take
+            // half a line each, whose other half must still be there for the next (1204 instead of 1380 at
+            // batch 1)
+            if constexpr (F64 || !ONCE) A[nu][j][l] = q[(j * L + l) * PST];
             else A[nu][j][l] = __builtin_nontemporal_load(q + (j * L + l) * PST);
         }
     };
@@ -297,19 +300,19 @@ __global__ __launch_bounds__(64 * W, SW > 1 && NBL == 16 ? 1 : 2) void stream_ke
 template <typename T>
 void launch(const StreamCall &k, hipStream_t s) {
     const blast_plan *p = k.plan;
-    auto go4 = [&](auto nct_, auto btt, auto nblt, auto nput, auto twot, auto swt, auto wt) {
+    auto go4 = [&](auto nct_, auto btt, auto nblt, auto nput, auto twot, auto oncet, auto swt, auto wt) {
         constexpr int NC = decltype(nct_)::value, BT = decltype(btt)::value, NBL = decltype(nblt)::value;
         constexpr int NPU = decltype(nput)::value, SW = decltype(swt)::value, W = decltype(wt)::value, TW = W / SW;
         const int nct = (k.batch + BT - 1) / BT, groups = (k.tiles.n + TW - 1) / TW;
         const int nsp = k.apart ? k.nsplit : 1, units = p->n_chi * nsp * groups * nct;
         for (int sp0 = 0; sp0 < k.nsplit; sp0 += nsp)
-            hipLaunchKernelGGL((stream_kernel<T, NC, BT, NBL, NPU, decltype(twot)::value, SW, W>),
+            hipLaunchKernelGGL((stream_kernel<T, NC, BT, NBL, NPU, decltype(twot)::value, decltype(oncet)::value, SW, W>),
                                dim3((unsigned)((units + 7) / 8 * 8)), dim3(64 * W), 0, s, (const T *)k.basis,
                                (const T *)k.c, k.cld, k.K_chi2, p->d_wR, k.batch, k.nbins, p->n_chi, p->n_R,
                                p->rows_pad, k.tiles, nct, k.nsplit, sp0, nsp, units, k.ybs, k.ysplit, (T *)k.Y,
                                (T *)k.w_out);
     };
-    auto go3 = [&](auto nct_, auto btt, auto nblt, auto nput, auto twot, auto swt) {
+    auto go3 = [&](auto nct_, auto btt, auto nblt, auto nput, auto twot, auto oncet, auto swt) {
         using std::integral_constant;
         if constexpr (sizeof(T) == 4) {
             constexpr int BT = decltype(btt)::value;
@@ -318,22 +321,24 @@ void launch(const StreamCall &k, hipStream_t s) {
             // 5 row tiles, 37 cosmologies 53.1 -> 46.5 us, 31 cosmologies of 128 nodes 58.7 -> 49.6; from three
             // work-groups per CU on the same or slower (540 of 12 tiles: 107.0 -> 107.9)
             if (w4 <= 512 && (w6 + 255) / 256 < (w4 + 255) / 256)
-                return go4(nct_, btt, nblt, nput, twot, swt, integral_constant<int, 6>());
+                return go4(nct_, btt, nblt, nput, twot, oncet, swt, integral_constant<int, 6>());
         }
-        go4(nct_, btt, nblt, nput, twot, swt, integral_constant<int, 4>());
+        go4(nct_, btt, nblt, nput, twot, oncet, swt, integral_constant<int, 4>());
     };
-    auto go2 = [&](auto nct_, auto btt, auto nblt, auto nput, auto twot) {
+    auto go2 = [&](auto nct_, auto btt, auto nblt, auto nput, auto twot, auto oncet) {
         using std::integral_constant;
         if constexpr (sizeof(T) == 8)
-            if (k.node_waves == 2) return go3(nct_, btt, nblt, nput, twot, integral_constant<int, 2>());
-        go3(nct_, btt, nblt, nput, twot, integral_constant<int, 1>());
+            if (k.node_waves == 2) return go3(nct_, btt, nblt, nput, twot, oncet, integral_constant<int, 2>());
+        go3(nct_, btt, nblt, nput, twot, oncet, integral_constant<int, 1>());
     };
-    // (only batches past the fused kernels' smallest take their two chains: the widest tiles)
+    // (only batches past the fused kernels' smallest take their two chains, and only batches past a tile more
+    // than one: the widest tiles)
     auto go = [&](auto nct_, auto btt, auto nblt, auto nput) {
         if constexpr (sizeof(T) == 4 && decltype(nblt)::value == 16) {
-            if (k.two_chains) return go2(nct_, btt, nblt, nput, std::true_type());
+            if (k.two_chains) return go2(nct_, btt, nblt, nput, std::true_type(), std::false_type());
+            if (k.batch > decltype(btt)::value) return go2(nct_, btt, nblt, nput, std::false_type(), std::false_type());
         }
-        go2(nct_, btt, nblt, nput, std::false_type());
+        go2(nct_, btt, nblt, nput, std::false_type(), std::true_type());
     };
     // rings as deep as the registers hold next to Y (256 per lane at two waves per SIMD)
     constexpr bool F64 = sizeof(T) == 8;
@@ -346,10 +351,11 @@ void launch(const StreamCall &k, hipStream_t s) {
         using B4 = integral_constant<int, 4>;
         using B8 = integral_constant<int, 8>;
         using B16 = integral_constant<int, 16>;
-        if (k.batch <= 4 && k.nbins <= 16) go(nct_, B4(), B4(), integral_constant<int, R4>());
-        else if (k.batch <= 4) go(nct_, B4(), B8(), integral_constant<int, R8>());
-        else if (k.batch <= 8 && k.nbins <= 16) go(nct_, B8(), B8(), integral_constant<int, R8>());
-        else if (k.nbins <= 16) go(nct_, B16(), B16(), integral_constant<int, R16>());
+        const int bt = stream_tile(k.batch, k.nbins);
+        if (bt == 4 && k.nbins <= 16) go(nct_, B4(), B4(), integral_constant<int, R4>());
+        else if (bt == 4) go(nct_, B4(), B8(), integral_constant<int, R8>());
+        else if (bt == 8 && k.nbins <= 16) go(nct_, B8(), B8(), integral_constant<int, R8>());
+        else if (bt == 16) go(nct_, B16(), B16(), integral_constant<int, R16>());
         else go(nct_, B8(), B16(), integral_constant<int, R16>());
     };
     switch (p->nc_pad / 32) {
