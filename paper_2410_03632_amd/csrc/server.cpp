@@ -9,9 +9,10 @@
 // arrival order into the forming set while the launch they would make still fits its arena
 // (admission by memory: requests with fewer bins take fewer bytes), launches the set when the
 // next request does not fit, when its oldest request has waited max_wait_ms or when no other set
-// runs (P in pinned memory is copied to its place while the set still forms): the requests' inputs go into the arena in the layout of the shape, the graph of the
-// smallest captured batch that holds them is replayed, C comes back to pinned host memory and
-// an event marks completion.  Sets launched while others run overlap on the device.
+// runs (P in pinned memory is copied to its place while the set still forms): the requests' inputs go
+// into the arena in the layout of the shape, the graph of the smallest captured batch that holds them
+// is replayed, C comes back to pinned host memory and an event marks completion.  Sets launched while
+// others run overlap on the device.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -38,6 +39,7 @@ struct Req {
     std::vector<int32_t> ell_idx;
     Clock::time_point t_submit;
     bool p_sent = false;  // P's copy into its place in the forming set's arena is on the set's stream
+    enum { kUnknown, kPinned, kPageable } p_mem = kUnknown;  // P's memory, asked for once
 };
 
 struct Done {
@@ -181,7 +183,8 @@ bool pinned(const void *p) {
 hipError_t send_ahead(blast_server *S, Set &st) {
     for (size_t k = 0; k < st.slots.size(); ++k) {
         Req &q = st.slots[k];
-        if (q.p_sent || !pinned(q.r.P)) continue;
+        if (q.p_mem == Req::kUnknown) q.p_mem = pinned(q.r.P) ? Req::kPinned : Req::kPageable;
+        if (q.p_sent || q.p_mem != Req::kPinned) continue;
         const hipError_t e =
             hipMemcpyAsync(st.arena + k * S->P_slot, q.r.P, S->P_slot, hipMemcpyHostToDevice, st.stream);
         if (e != hipSuccess) return e;
