@@ -39,6 +39,7 @@ struct Req {
     std::vector<int32_t> ell_idx;
     Clock::time_point t_submit;
     bool p_sent = false;  // P's copy into its place in the forming set's arena is on the set's stream
+    bool p_started = false;  // a copy of P, to this place or an earlier one, may be on its way
     enum { kUnknown, kPinned, kPageable } p_mem = kUnknown;  // P's memory, asked for once
 };
 
@@ -64,7 +65,7 @@ struct Set {
     double *C_host = nullptr;  // pinned
     double *K1_host = nullptr; // pinned: K_chi of a launch's requests
     std::vector<Graph> graphs;
-    hipEvent_t done = nullptr;
+    hipEvent_t done = nullptr, sent = nullptr;  // a launch's results are there; the copies sent ahead have ended
     std::vector<Req> slots;
     int G = 0;              // clustering-bin bucket of the requests admitted so far
     int run_batch = 0, run_G = 0;
@@ -181,6 +182,7 @@ bool pinned(const void *p) {
 // in flight and the wait for more requests.  Only from pinned memory, whose copies enqueue at once (the
 // caller holds the server's lock); others go with the launch.
 hipError_t send_ahead(blast_server *S, Set &st) {
+    bool any = false;
     for (size_t k = 0; k < st.slots.size(); ++k) {
         Req &q = st.slots[k];
         if (q.p_mem == Req::kUnknown) q.p_mem = pinned(q.r.P) ? Req::kPinned : Req::kPageable;
@@ -188,9 +190,9 @@ hipError_t send_ahead(blast_server *S, Set &st) {
         const hipError_t e =
             hipMemcpyAsync(st.arena + k * S->P_slot, q.r.P, S->P_slot, hipMemcpyHostToDevice, st.stream);
         if (e != hipSuccess) return e;
-        q.p_sent = true;
+        q.p_sent = q.p_started = any = true;
     }
-    return hipSuccess;
+    return any ? hipEventRecord(st.sent, st.stream) : hipSuccess;
 }
 
 hipError_t launch_set(blast_server *S, Set &st) {
@@ -394,6 +396,7 @@ void free_sets(blast_server *S) {
         if (st.C_host) (void)hipHostFree(st.C_host);
         if (st.K1_host) (void)hipHostFree(st.K1_host);
         if (st.done) (void)hipEventDestroy(st.done);
+        if (st.sent) (void)hipEventDestroy(st.sent);
         if (st.stream) (void)hipStreamDestroy(st.stream);
     }
     S->sets.clear();
@@ -447,6 +450,7 @@ extern "C" blast_status blast_server_create(blast_plan *plan, const blast_server
     for (Set &st : S->sets) {
         if (e == hipSuccess) e = hipStreamCreate(&st.stream);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&st.done, hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&st.sent, hipEventDisableTiming);
         if (e == hipSuccess) e = hipMalloc((void **)&st.arena, S->set_bytes);
         if (e == hipSuccess) e = hipHostMalloc((void **)&st.C_host, c_host, hipHostMallocDefault);
         if (e == hipSuccess)
@@ -571,7 +575,7 @@ extern "C" blast_status blast_server_submit(blast_server *S, const blast_request
 
 extern "C" blast_status blast_server_cancel(blast_server *S, uint64_t ticket) {
     if (!S) return blast::set_error("NULL argument"), BLAST_E_INVALID;
-    std::lock_guard<std::mutex> lk(S->mu);
+    std::unique_lock<std::mutex> lk(S->mu);
     const Clock::time_point now = Clock::now();
     for (auto it = S->queue.begin(); it != S->queue.end(); ++it)
         if (it->id == ticket) {
@@ -585,14 +589,18 @@ extern "C" blast_status blast_server_cancel(blast_server *S, uint64_t ticket) {
         Set &st = S->sets[S->forming];
         for (auto it = st.slots.begin(); it != st.slots.end(); ++it)
             if (it->id == ticket) {
-                // P copies on their way end before their requests can; the requests behind this one move up a
-                // place and are sent again
-                if (std::any_of(st.slots.begin(), st.slots.end(), [](const Req &q) { return q.p_sent; }))
-                    (void)hipStreamSynchronize(st.stream);
-                finish(S, *it, BLAST_E_CANCELLED, now);
+                const Req q = std::move(*it);
+                // the requests behind this one move up a place and are sent again
                 for (auto b = st.slots.erase(it); b != st.slots.end(); ++b) b->p_sent = false;
                 st.G = 0;
-                for (const Req &q : st.slots) st.G = std::max(st.G, bucket_of(S, q.r.n_g));
+                for (const Req &r : st.slots) st.G = std::max(st.G, bucket_of(S, r.r.n_g));
+                // a copy of its own P on the way ends before the request does; others go on meanwhile
+                if (q.p_started) {
+                    lk.unlock();
+                    (void)hipEventSynchronize(st.sent);
+                    lk.lock();
+                }
+                finish(S, q, BLAST_E_CANCELLED, Clock::now());
                 S->cancelled++;
                 S->cv_done.notify_all();
                 return BLAST_OK;

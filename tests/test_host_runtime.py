@@ -77,7 +77,48 @@ def pageable_requests_are_asked_once(B, F):
     s.done()
 
 
-CASES = [pageable_requests_are_asked_once]
+def _in_thread(f):
+    t = threading.Thread(target=f, daemon=True)
+    t.start()
+    return t
+
+
+def cancelling_waits_for_its_own_copy_only(B, F):
+    s = _Server(B, F)
+    (ta, a), (tb, _), (tc, c), (td, d) = s.submit(True), s.submit(False), s.submit(True), s.submit(True)
+    s.until(lambda: s.pending(a) and s.pending(c) and s.pending(d))
+    t = _in_thread(lambda: s.srv.cancel(tb))  # nothing of it is on the way
+    t.join(5)
+    assert not t.is_alive()
+    s.until(lambda: s.pending(c) == 2 and s.pending(d) == 2)  # moved up and sent again
+    left = []
+
+    def cancel(ticket, P):
+        s.srv.cancel(ticket)
+        left.append(s.pending(P))
+
+    ts = [_in_thread(lambda: cancel(ta, a)), _in_thread(lambda: cancel(tc, c))]
+    time.sleep(0.1)
+    assert all(t.is_alive() for t in ts)
+    t = _in_thread(s.srv.stats)  # others are not kept waiting
+    t.join(5)
+    assert not t.is_alive()
+    F.fake_hold(0)
+    for t in ts:
+        t.join(5)
+    assert left == [0, 0]
+    for ticket in (ta, tb, tc):
+        try:
+            s.srv.wait(ticket, 5000)
+            assert False
+        except B.BlastError as e:
+            assert e.status == B.E_CANCELLED
+    s.srv.wait(td, 5000)
+    assert s.srv.stats()["cancelled"] == 3
+    s.done()
+
+
+CASES = [pageable_requests_are_asked_once, cancelling_waits_for_its_own_copy_only]
 
 
 @pytest.mark.parametrize("case", [c.__name__ for c in CASES])
