@@ -321,9 +321,10 @@ void scheduler(blast_server *S) {
                 S->queue.pop_front();
             }
             if (S->forming >= 0) {
-                (void)hipStreamSynchronize(S->sets[S->forming].stream);  // no copy may outlive its request
-                for (const Req &q : S->sets[S->forming].slots) finish(S, q, S->fatal, now);
-                S->sets[S->forming].slots.clear();
+                Set &st = S->sets[S->forming];
+                if (!st.slots.empty()) (void)hipStreamSynchronize(st.stream);  // no copy may outlive its request
+                for (const Req &q : st.slots) finish(S, q, S->fatal, now);
+                st.slots.clear();
                 S->forming = -1;
             }
             S->cv_done.notify_all();
@@ -369,6 +370,7 @@ void scheduler(blast_server *S) {
                 S->max_sets_in_flight = std::max<int64_t>(S->max_sets_in_flight, running + 1);
                 lk.unlock();
                 const hipError_t e = launch_set(S, st);
+                if (e != hipSuccess) (void)hipStreamSynchronize(st.stream);  // no copy may outlive its request
                 lk.lock();
                 if (e != hipSuccess) {
                     S->fatal = BLAST_E_HIP;

@@ -118,7 +118,29 @@ def cancelling_waits_for_its_own_copy_only(B, F):
     s.done()
 
 
-CASES = [pageable_requests_are_asked_once, cancelling_waits_for_its_own_copy_only]
+def a_failed_launch_ends_after_its_copies(B, F):
+    s = _Server(B, F, max_wait_ms=300.0)
+    F.fake_fail_graph(1)
+    (ta, a), (tb, b) = s.submit(True), s.submit(False)
+    st = []
+
+    def wait(t):
+        try:
+            s.srv.wait(t)
+        except B.BlastError as e:
+            st.append((e.status, s.pending(a), s.pending(b)))
+
+    ts = [_in_thread(lambda: wait(ta)), _in_thread(lambda: wait(tb))]
+    s.until(lambda: s.pending(a) and s.pending(b))  # b with the launch, after 300 ms
+    time.sleep(0.2)
+    F.fake_hold(0)
+    for t in ts:
+        t.join(5)
+    assert st == [(B.E_HIP, 0, 0)] * 2, st
+    s.done()
+
+
+CASES = [pageable_requests_are_asked_once, cancelling_waits_for_its_own_copy_only, a_failed_launch_ends_after_its_copies]
 
 
 @pytest.mark.parametrize("case", [c.__name__ for c in CASES])
