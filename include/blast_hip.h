@@ -78,14 +78,15 @@ typedef enum {
  * bins (P rows split into FP16 hi + lo inside the contraction kernel; with 17-20 bins P is
  * split by the coefficient-input conversion instead of projected); FP32 on FP32 P with
  * n_cheb % 4 == 0 (P rows read in place of the padded coefficient rows); FP64 on FP64 P
- * with an even n_cheb (likewise; a plan that has no room for the FP64 nodal basis and whose
- * n_cheb is not a multiple of 32 does without it and projects).  The backward on such calls
- * computes dP = B^T dw likewise (FP32: n_cheb a multiple of 32).  The result is that of the projection route up to rounding; on the ridge R ~ 1 the terms
- * B_j P_j are quadrature weights of one sign, so the sum cancels far less than the
- * Chebyshev terms do and the error of the mixed paths drops on the named workloads
- * (figures below; on small grids with k up to 0.6/Mpc the two routes trade places, both
- * within 1e-4).  Other calls (FP64 P on FP32 or FP16X3, coefficient input, BF16 paths)
- * project per call.
+ * with an even n_cheb (likewise; if it is not a multiple of 32, only in plans whose
+ * `precisions` name FP64 and, when the plan was made, twice the FP64 nodal basis was still
+ * free: other plans project).  The backward on such calls computes dP = B^T dw likewise
+ * (FP32: n_cheb a multiple of 32).  The result is that of the projection route up to
+ * rounding; on the ridge R ~ 1 the terms B_j P_j are quadrature weights of one sign, so the
+ * sum cancels far less than the Chebyshev terms do and the error of the mixed paths drops on
+ * the named workloads (figures below; on small grids with k up to 0.6/Mpc the two routes
+ * trade places, both within 1e-4).  Other calls (FP64 P on FP32 or FP16X3, coefficient
+ * input, BF16 paths) project per call.
  * The basis precompute is always FP64; the quadrature always accumulates in FP64.
  *
  * Accuracy.  The relative error of C against exact arithmetic on the same grids is about
@@ -157,7 +158,8 @@ typedef struct {
     int32_t n_cheb;       /* Chebyshev nodes = coefficients, 2..128                  */
     uint32_t types;       /* subset of BLAST_GG | BLAST_GS | BLAST_SS                */
     uint32_t precisions;  /* bitmask of (1 << blast_precision) kept resident; FP64
-                             is always built                                        */
+                             is always built (by name also with its nodal basis where
+                             that is optional, see above)                           */
     int32_t kq_panels;    /* k-quadrature: coarse panels uniform in arccos(x);
                              0 = n_cheb                                              */
     double kq_phase;      /* k-quadrature: max Bessel phase (chi1+chi2) dk per

@@ -271,6 +271,7 @@ static blast_status plan_create_impl(const blast_plan_desc *d, int32_t device, B
     blast_grid_k_cheb(d->n_cheb, d->k_min, d->k_max, p->knodes.data());
     p->kq_panels = d->kq_panels ? d->kq_panels : d->n_cheb;
     p->kq_phase = d->kq_phase > 0 ? d->kq_phase : 8.0;
+    p->asked = d->precisions;
     p->precisions = d->precisions | 1u;
 
     DeviceGuard guard(device);
@@ -439,7 +440,7 @@ extern "C" blast_status blast_plan_save(const blast_plan *p, const char *path) {
     Writer w{f};
     w.put(kMagic, 8);
     const int32_t hdr[8] = {(int32_t)kFileVersion, p->n_ell, p->n_chi, p->n_R, p->n_cheb, (int32_t)p->types,
-                            (int32_t)p->precisions, p->kq_panels};
+                            (int32_t)p->asked, p->kq_panels};
     w.put(hdr, sizeof(hdr));
     const double hd[3] = {p->kmin, p->kmax, p->kq_phase};
     w.put(hd, sizeof(hd));

@@ -788,19 +788,17 @@ blast_status derive_precisions(blast_plan *p, hipStream_t s) {
                                p->rows_pad, p->nc_pad, p->n_cheb, nullptr, nullptr, nullptr, p->basis.nf32, nullptr);
         }
     }
-    // FP64 nodal P read as c, in whole 16-byte granules.  (Unpadded rows can also be projected: a plan that
-    // has no room for the copy does without it.)
-    if ((p->precisions & (1u << BLAST_FP64)) && p->n_cheb % 2 == 0) {
-        hipError_t e = hipMalloc(&p->basis.nf64, n * sizeof(double));
-        if (e != hipSuccess) {
-            p->basis.nf64 = nullptr;
-            if (p->n_cheb == p->nc_pad || e != hipErrorOutOfMemory) return fail(e, "FP64 nodal basis");
-            (void)hipGetLastError();
-        } else {
-            const unsigned g = (unsigned)std::min<size_t>((nrows + 3) / 4, 2048);
-            hipLaunchKernelGGL(to_nodal_kernel<64>, dim3(g), dim3(256), 0, s, p->basis.f64, p->d_dctn64, nrows,
-                               p->rows_pad, p->nc_pad, p->n_cheb, nullptr, nullptr, nullptr, nullptr, p->basis.nf64);
-        }
+    const auto make_nf64 = [&] {  // FP64 nodal P read as c, in whole 16-byte granules
+        const hipError_t e = hipMalloc(&p->basis.nf64, n * sizeof(double));
+        if (e != hipSuccess) return p->basis.nf64 = nullptr, e;
+        const unsigned g = (unsigned)std::min<size_t>((nrows + 3) / 4, 2048);
+        hipLaunchKernelGGL(to_nodal_kernel<64>, dim3(g), dim3(256), 0, s, p->basis.f64, p->d_dctn64, nrows,
+                           p->rows_pad, p->nc_pad, p->n_cheb, nullptr, nullptr, nullptr, nullptr, p->basis.nf64);
+        return hipSuccess;
+    };
+    if (p->n_cheb == p->nc_pad) {
+        const hipError_t e = make_nf64();
+        if (e != hipSuccess) return fail(e, "FP64 nodal basis");
     }
     const bool want_hi = p->precisions & ((1u << BLAST_BF16) | (1u << BLAST_BF16X3));
     const bool want_lo = p->precisions & (1u << BLAST_BF16X3);
@@ -844,6 +842,18 @@ blast_status derive_precisions(blast_plan *p, hipStream_t s) {
         }
     }
     BLAST_HIP_TRY(hipGetLastError());
+    // With n_cheb no multiple of 32, FP64 calls on nodal P can also project: their nodal basis is made for plans
+    // asked for FP64 by name, after all that the plan has to have, and only if it leaves free as much again for
+    // the calls' own memory.
+    if ((p->asked & (1u << BLAST_FP64)) && p->n_cheb % 2 == 0 && p->n_cheb != p->nc_pad) {
+        size_t left = 0, total = 0;
+        BLAST_HIP_TRY(hipMemGetInfo(&left, &total));
+        if (left >= 2 * n * sizeof(double)) {
+            const hipError_t e = make_nf64();
+            if (e != hipSuccess && e != hipErrorOutOfMemory) return fail(e, "FP64 nodal basis");
+            (void)hipGetLastError();
+        }
+    }
     return BLAST_OK;
 }
 

@@ -94,6 +94,7 @@ struct blast_plan {
     double kq_phase = 0;
     int64_t kq_nodes = 0;
     double build_ms = 0;
+    uint32_t asked = 0;  // the caller's mask; `precisions` has FP64 in any case
     uint32_t precisions = 0;
     // device data
     blast::BasisBuffers basis;

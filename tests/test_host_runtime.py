@@ -4,6 +4,7 @@ import ctypes
 import os
 import subprocess
 import sys
+import tempfile
 import threading
 import time
 import traceback
@@ -140,7 +141,46 @@ def a_failed_launch_ends_after_its_copies(B, F):
     s.done()
 
 
-CASES = [pageable_requests_are_asked_once, cancelling_waits_for_its_own_copy_only, a_failed_launch_ends_after_its_copies]
+def the_optional_nodal_copy_comes_last(B, F):
+    """The FP64 nodal basis of an even n_cheb that is no multiple of 32: only for plans asked for FP64, and only out
+    of memory that nothing else of the plan needs and that leaves as much again."""
+    size = dict(n_chi=256, n_R=96, n_ell=60, n_cheb=34)
+    n = 256 * 96 * 192 * 64 * 8  # rows of 3 types x 60 multipoles and columns padded: bytes of one FP64 copy
+
+    def make(budget, precisions):
+        F.fake_budget(budget)
+        p = _plan(B, precisions=precisions, **size)
+        got = p.basis_bytes[0], F.fake_used()
+        p.close()
+        assert F.fake_used() == 0
+        return got
+
+    room = 1 << 40
+    every = ("fp64", "fp32", "bf16x3")
+    assert make(room, ())[0] == make(room, ("fp32",))[0] == make(room, ("bf16x3", "fp16x3"))[0] == n
+    has, full = make(room, every)
+    assert has == 2 * n
+    assert make(full + n, every) == (2 * n, full)
+    for budget in (full + n - 1, full, full - 1, full - n):  # the last: just what the plan has to have
+        assert make(budget, every) == (n, full - n), budget
+    try:
+        make(full - n - 1, every)
+        assert False
+    except B.BlastError as e:
+        assert e.status == B.E_OOM
+    F.hipGetLastError()
+    F.fake_budget(room)
+    with tempfile.TemporaryDirectory() as d:  # a saved plan comes back with what it was asked for
+        for precisions in (("bf16x3",), ("fp64", "fp32")):
+            p = _plan(B, n_cheb=34, precisions=precisions)
+            p.save(d + "/p")
+            q = B.Plan.load(d + "/p")
+            assert p.basis_bytes == q.basis_bytes
+            p.close(), q.close()
+
+
+CASES = [pageable_requests_are_asked_once, cancelling_waits_for_its_own_copy_only, a_failed_launch_ends_after_its_copies,
+         the_optional_nodal_copy_comes_last]
 
 
 @pytest.mark.parametrize("case", [c.__name__ for c in CASES])
