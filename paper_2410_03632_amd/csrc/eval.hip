@@ -2345,10 +2345,11 @@ __global__ __launch_bounds__(256, NBT == 1 ? (sizeof(YT) == 8 ? 3 : 4) : 2) void
     extern __shared__ __align__(16) double smem_c[];
     const int nbins = ng + ns;
     const int nc4 = (n_chi + 3) & ~3;
-    // [nc4][NBP], bin b of node a at b ^ (a & 15): the 16 lanes of a K-step read the 16 bins of one chi
-    // node, and the lanes that fill the table write one bin of 16 nodes, from and to 16 places of a row
+    // [nc4 + 1][NBP], bin b of node a at b ^ (a & 15): the 16 lanes of a K-step read the 16 bins of one chi
+    // node, and the lanes that fill the table write one bin of 16 nodes, from and to 16 places of a row.  Row
+    // nc4 is zero, for K-steps past the last node (a node's own row would make NaN of an infinite kernel)
     double *Kt = smem_c;
-    double *Zs = smem_c + (size_t)NBP * nc4;       // [4 waves][NBP][NBP]
+    double *Zs = smem_c + (size_t)NBP * (nc4 + 1);  // [4 waves][NBP][NBP]
     const int nblk = (sel.n_out + CR - 1) / CR;
     const int slot = blockIdx.x / nblk, io0 = (blockIdx.x % nblk) * CR;
     const int beta = blockIdx.y;
@@ -2383,6 +2384,7 @@ __global__ __launch_bounds__(256, NBT == 1 ? (sizeof(YT) == 8 ? 3 : 4) : 2) void
         __builtin_amdgcn_sched_barrier(0);
     };
     load_block(0);
+    if (threadIdx.x < NBP) Kt[nc4 * NBP + threadIdx.x] = 0.0;
     // table: wave wv takes bins wv, wv + 4, ..., a lane consecutive chi nodes (whole lines of K_chi)
     for (int a0 = 0; a0 < nc4; a0 += 128) {
         double kv[2][NBP / 4], wc[2];
@@ -2443,8 +2445,8 @@ __global__ __launch_bounds__(256, NBT == 1 ? (sizeof(YT) == 8 ? 3 : 4) : 2) void
             if (s0) load_block(s0);
 #pragma unroll
             for (int u = 0; u < KB; ++u) {
-                if (u % 8 == 0 && s0 + u >= nsteps) break;  // uniform; the last 8 masked
-                const int a = 4 * (s0 + u) + lk, ac = min(a, nc4 - 1);
+                if (u % 8 == 0 && s0 + u >= nsteps) break;  // uniform; the last 8 meet the zero row
+                const int a = 4 * (s0 + u) + lk, ac = min(a, nc4);
                 double av[NBT], b[NBT];
 #pragma unroll
                 for (int i = 0; i < NBT; ++i) {
@@ -3901,7 +3903,7 @@ void stage_quad_c(blast_plan *p, const blast_cl_args *a, const Ctx &x, const voi
         constexpr int NBT = decltype(nbt)::value;
         if (few)
             hipLaunchKernelGGL((quad_c_few_kernel<YT, NBT>), dim3((unsigned)(p->nt * ((x.sel.n_out + 3) / 4)), a->batch),
-                               dim3(256), sh2, s, (const YT *)Y, sy.nsplit, sy.ysplit, a->K_chi, p->d_wchi, p->d_chi,
+                               dim3(256), sh2 + x.nbp * sizeof(double), s, (const YT *)Y, sy.nsplit, sy.ysplit, a->K_chi, p->d_wchi, p->d_chi,
                                p->d_pref, p->n_chi, p->rows_pad, p->n_ell, st, x.ng, x.ns, a->types, x.npairs, x.sel,
                                a->C);
         else
