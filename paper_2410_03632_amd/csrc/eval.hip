@@ -3061,6 +3061,12 @@ __global__ __launch_bounds__(256) void adj_w64_mfma_kernel(const double *__restr
 #pragma unroll
             for (int u = 0; u < CH; ++u) {
                 if (c0 + u >= RTn) break;
+                // rows that pad the last tile: zero times their w is not zero where a coefficient is infinite
+                const int left = rows - 16 * (c0 + u) - 4 * lk;
+                if (16 * (c0 + u) + 16 > rows) {  // (uniform)
+                    x[u][0].x = left > 0 ? x[u][0].x : 0.0, x[u][0].y = left > 1 ? x[u][0].y : 0.0;
+                    x[u][1].x = left > 2 ? x[u][1].x : 0.0, x[u][1].y = left > 3 ? x[u][1].y : 0.0;
+                }
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) {
                     const double *yt = dYt + (size_t)(16 * q + lr) * ds + 16 * (c0 + u) + 4 * lk;
