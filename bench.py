@@ -116,6 +116,41 @@ def fused_path(prec, nbins, batch):
     return nbins <= 20 and (batch >= 32 or prec == "fp16x3")
 
 
+def launch_stages(per_launch, plan, cfg, prec, batch):
+    """(ms per launch, algorithmic work, kernel) of each stage, from the library's four event intervals.  Fused
+    calls have the R-quadrature weights in the second interval and contraction + R-quadrature in the
+    third; smaller FP64 and FP32 calls that stream the basis run one kernel for both and no weights table, which
+    leaves the second interval empty where w's route has its longest kernel."""
+    work = stage_work(plan, cfg, prec, batch)
+    fused = fused_path(prec, cfg.n_g + cfg.n_s, batch)
+    p = per_launch
+    streamed = not fused and prec in ("fp64", "fp32") and p["contraction"] < 0.2 * p["quad_R"]
+    split = {"fp64": "project_split64_kernel", "fp16x3": "project_h16_kernel"}.get(prec, "project_split_kernel")
+    kernel = {"projection": split if cfg.n_cheb % 8 == 0 else "project_kernel", "contraction": "contract_kernel",
+              "quad_R": "quad_y_kernel", "quad_chi": "quad_c_mfma_kernel", "r_weights": "kt_kernel"}
+    if streamed:
+        ms = {"projection": p["projection"], "contraction": p["quad_R"], "quad_chi": p["quad_chi"]}
+        eb = 8 if prec == "fp64" else 4
+        NP, nb = cfg.n_chi * cfg.n_R, cfg.n_g + cfg.n_s
+        rows_bins = plan.n_ell * (cfg.n_g + nb + cfg.n_s)
+        y_bytes = cfg.n_chi * plan.rows_pad * (16 if nb <= 16 else 32) * eb * batch
+        work = {k: v for k, v in work.items() if k in ms}
+        work["contraction"] = dict(
+            flops=2.0 * plan.rows * cfg.n_cheb * NP * batch + 2.0 * rows_bins * NP * batch,
+            bytes=float(NP * plan.rows * cfg.n_cheb * eb + NP * cfg.n_cheb * eb * batch + nb * NP * 8 * batch + y_bytes))
+        kernel["contraction"] = "stream_kernel"
+    elif fused:
+        ms = {"projection": p["projection"], "r_weights": p["contraction"], "contraction": p["quad_R"],
+              "quad_chi": p["quad_chi"]}
+        kernel["contraction"] = "contract_quad_f64_kernel" if prec == "fp64" else \
+            "contract_quad_wide_kernel" if prec == "fp16x3" and cfg.n_g + cfg.n_s <= 16 else "contract_quad_kernel"
+    else:
+        ms = dict(p)
+    if nodal_path(prec, cfg):
+        del ms["projection"]  # nothing runs there
+    return ms, work, kernel
+
+
 def B_pairs(cfg):
     g, s = cfg.n_g, cfg.n_s
     return g * (g + 1) // 2 + g * s + s * (s + 1) // 2
@@ -582,23 +617,10 @@ def main():
     ms_per_step = (t1 - t0) * 1e3 / args.steps
     value = Bn / (ms_per_step * 1e-3)
     per_launch = {k: v / max(ncalls, 1) for k, v in stage_ms.items()}
-    fused = fused_path(prec, cfg.n_g + cfg.n_s, Bn)
-    if fused:
-        # intervals of the fused path: R-quadrature weights, then contraction + R-quadrature
-        per_launch = {"projection": per_launch["projection"], "r_weights": per_launch["contraction"],
-                      "contraction": per_launch["quad_R"], "quad_chi": per_launch["quad_chi"]}
-    if nodal_path(prec, cfg):
-        del per_launch["projection"]  # nothing runs there
+    per_launch, work, kernel_of = launch_stages(per_launch, plan, cfg, prec, Bn)
     log("ms/step %.3f  sets/s %.1f  stages(ms/launch) %s" % (ms_per_step, value, per_launch))
-    work = stage_work(plan, cfg, prec, Bn)
-    dom = max(per_launch, key=per_launch.get)
+    dom = max((k for k in per_launch if k in work), key=per_launch.get)
     roof = roofline(work[dom], per_launch[dom], prec)
-    split = {"fp64": "project_split64_kernel", "fp16x3": "project_h16_kernel"}.get(prec, "project_split_kernel")
-    kernel_of = {"projection": split if cfg.n_cheb % 8 == 0 else "project_kernel",
-                 "contraction": (("contract_quad_f64_kernel" if prec == "fp64" else
-                                  "contract_quad_wide_kernel" if prec == "fp16x3" and cfg.n_g + cfg.n_s <= 16
-                                  else "contract_quad_kernel") if fused else "contract_kernel"),
-                 "quad_R": "quad_y_kernel", "quad_chi": "quad_c_mfma_kernel", "r_weights": "kt_kernel"}
     roof["kernel"] = kernel_of[dom]
     roof["traffic"] = counter_traffic(roof["kernel"], cfg.name, Bn, prec)
     roof["stage_ms_per_launch"] = per_launch
@@ -769,7 +791,7 @@ def main():
     if args.serving_seconds > 0:
         log("serving run: %.1f s of arrivals at 200 requests/s" % args.serving_seconds)
         plan.close()
-        # the server runs the FP32 path: at its small batches the unfused kernels are faster
+        # the server runs the FP32 path: at its small batches streaming the basis is faster than the fused kernels
         serving = serving_run(args.serving_seconds, precision="fp32")
         log("serving: %s" % serving)
 
