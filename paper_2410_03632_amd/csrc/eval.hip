@@ -2334,13 +2334,11 @@ __global__ __launch_bounds__(256) void quad_c_mfma_kernel(const YT *__restrict__
 // one per wave, with the first loads of Y ahead of the K table and whole lines of K_chi read for it.  Y may
 // be the sum of nsplit ranges, ysplit values apart.  The sums over the chi nodes run in the same order.
 template <typename YT, int NBT>
-__global__ __launch_bounds__(256, NBT == 1 ? (sizeof(YT) == 8 ? 3 : 4) : 2) void quad_c_few_kernel(const YT *__restrict__ Y, int nsplit, size_t ysplit,
-                                                          const double *__restrict__ Kchi,
-                                                          const double *__restrict__ wchi,
-                                                          const double *__restrict__ chi,
-                                                          const double *__restrict__ pref, int n_chi, int rows_pad,
-                                                          int n_ell, Slots slot_type, int ng, int ns, uint32_t types,
-                                                          int npairs, EllSel sel, double *__restrict__ C) {
+__global__ __launch_bounds__(256, NBT == 1 ? (sizeof(YT) == 8 ? 3 : 4) : 2) void quad_c_few_kernel(
+    const YT *__restrict__ Y, int nsplit, size_t ysplit, const double *__restrict__ Kchi,
+    const double *__restrict__ wchi, const double *__restrict__ chi, const double *__restrict__ pref, int n_chi,
+    int rows_pad, int n_ell, Slots slot_type, int ng, int ns, uint32_t types, int npairs, EllSel sel,
+    double *__restrict__ C) {
     constexpr int NBP = 16 * NBT, CR = 4;
     extern __shared__ __align__(16) double smem_c[];
     const int nbins = ng + ns;
@@ -2845,11 +2843,11 @@ __device__ inline bool chi_cosmology(int n_chi, int batch, int &a, int &beta) {
 }
 inline dim3 chi_cosmology_grid(int n_chi, int batch) { return dim3((unsigned)((n_chi * batch + 7) / 8 * 8)); }
 
-template <typename T, int NB>
-__global__ __launch_bounds__(256) void adj_w_kernel(const T *__restrict__ dY, const T *__restrict__ w,
+template <int NB>
+__global__ __launch_bounds__(256) void adj_w_kernel(const double *__restrict__ dY, const double *__restrict__ w,
                                                     const double *__restrict__ Kchi2, const double *__restrict__ wR,
                                                     int batch, int NP, int nR, int n_chi, int rows, int rows_pad,
-                                                    int nbins, T *__restrict__ dw, double *__restrict__ dK2) {
+                                                    int nbins, double *__restrict__ dw, double *__restrict__ dK2) {
     constexpr int DS = adj_w_stride<NB>();
     extern __shared__ __align__(16) unsigned char smem_a[];
     double *Kh = (double *)smem_a;                   // [nR][NB]
@@ -2862,7 +2860,7 @@ __global__ __launch_bounds__(256) void adj_w_kernel(const T *__restrict__ dY, co
     }
     for (int i = threadIdx.x; i < rows_pad * NB; i += blockDim.x) {
         const int row = i / NB, m = i % NB;
-        dYa[row * DS + m] = row < rows ? (double)dY[(((size_t)beta * rows_pad + row) * n_chi + a) * NB + m] : 0.0;
+        dYa[row * DS + m] = row < rows ? dY[(((size_t)beta * rows_pad + row) * n_chi + a) * NB + m] : 0.0;
     }
     __syncthreads();
     const size_t base = ((size_t)beta * NP + (size_t)a * nR) * rows_pad;
@@ -2877,16 +2875,16 @@ __global__ __launch_bounds__(256) void adj_w_kernel(const T *__restrict__ dY, co
             double v = 0.0;
 #pragma unroll
             for (int m = 0; m < NB; ++m) v += Kh[b * NB + m] * yr[m];
-            dw[base + (size_t)b * rows_pad + row] = (T)v;
+            dw[base + (size_t)b * rows_pad + row] = v;
         }
     }
     if (dK2) {
         for (int i = threadIdx.x; i < nR * NB; i += blockDim.x) {
             const int b = i / NB, m = i % NB;
             if (m >= nbins) continue;
-            const T *wr = w + base + (size_t)b * rows_pad;
+            const double *wr = w + base + (size_t)b * rows_pad;
             double v = 0.0;
-            for (int row = 0; row < rows; ++row) v += dYa[row * DS + m] * (double)wr[row];
+            for (int row = 0; row < rows; ++row) v += dYa[row * DS + m] * wr[row];
             dK2[(((size_t)beta * nbins + m) * n_chi + a) * nR + b] = wR[b] * v;
         }
     }
@@ -3481,9 +3479,11 @@ hipError_t allow_large_lds() {
         const void *fns[] = {
             (const void *)quad_y_kernel<double, 16>, (const void *)quad_y_kernel<double, 32>,
             (const void *)quad_y_kernel<float, 16>, (const void *)quad_y_kernel<float, 32>,
-            (const void *)quad_c_mfma_kernel<double, 1>, (const void *)quad_c_few_kernel<double, 1>, (const void *)quad_c_mfma_kernel<double, 2>, (const void *)quad_c_few_kernel<double, 2>,
-            (const void *)quad_c_mfma_kernel<float, 1>, (const void *)quad_c_few_kernel<float, 1>, (const void *)quad_c_mfma_kernel<float, 2>, (const void *)quad_c_few_kernel<float, 2>,
-            (const void *)adj_w_kernel<double, 16>, (const void *)adj_w_kernel<double, 32>,
+            (const void *)quad_c_mfma_kernel<double, 1>, (const void *)quad_c_mfma_kernel<double, 2>,
+            (const void *)quad_c_mfma_kernel<float, 1>, (const void *)quad_c_mfma_kernel<float, 2>,
+            (const void *)quad_c_few_kernel<double, 1>, (const void *)quad_c_few_kernel<double, 2>,
+            (const void *)quad_c_few_kernel<float, 1>, (const void *)quad_c_few_kernel<float, 2>,
+            (const void *)adj_w_kernel<16>, (const void *)adj_w_kernel<32>,
             (const void *)adj_w64_mfma_kernel<16>, (const void *)adj_w64_mfma_kernel<32>,
             (const void *)contract_t_kernel<16>, (const void *)contract_t_kernel<kAdjBT>,
             (const void *)adj_project_split64_kernel<double, 4>, (const void *)adj_project_split64_kernel<float, 4>,
@@ -3909,9 +3909,9 @@ void stage_quad_c(blast_plan *p, const blast_cl_args *a, const Ctx &x, const voi
         constexpr int NBT = decltype(nbt)::value;
         if (few)
             hipLaunchKernelGGL((quad_c_few_kernel<YT, NBT>), dim3((unsigned)(p->nt * ((x.sel.n_out + 3) / 4)), a->batch),
-                               dim3(256), sh2 + x.nbp * sizeof(double), s, (const YT *)Y, sy.nsplit, sy.ysplit, a->K_chi, p->d_wchi, p->d_chi,
-                               p->d_pref, p->n_chi, p->rows_pad, p->n_ell, st, x.ng, x.ns, a->types, x.npairs, x.sel,
-                               a->C);
+                               dim3(256), sh2 + x.nbp * sizeof(double), s, (const YT *)Y, sy.nsplit, sy.ysplit,
+                               a->K_chi, p->d_wchi, p->d_chi, p->d_pref, p->n_chi, p->rows_pad, p->n_ell, st, x.ng,
+                               x.ns, a->types, x.npairs, x.sel, a->C);
         else
             hipLaunchKernelGGL((quad_c_mfma_kernel<YT, NBT>), dim3((unsigned)(p->nt * nblk), a->batch), dim3(256), sh2, s,
                                (const YT *)Y, a->K_chi, p->d_wchi, p->d_chi, p->d_pref, p->n_chi, p->rows_pad, p->n_ell,
@@ -4259,12 +4259,14 @@ blast_status backward(blast_plan *p, const blast_cl_args *a, const double *dC, v
             /* 64 chi nodes per work-group once that makes one per CU, else 16 with the rows over 8 waves */      \
             if ((long)((p->n_chi + 63) / 64) * a->batch >= 256)                                                   \
                 hipLaunchKernelGGL((adj_kchi_kernel<T, NB, 64 / NB, 4>),                                          \
-                                   dim3((unsigned)((p->n_chi + 1024 / NB - 1) / (1024 / NB)), a->batch), dim3(256), 0, s, \
-                                   (const T *)Y, Sg, p->d_wchi, p->d_chi, p->n_chi, p->rows, p->rows_pad, x.nbins, dK_chi); \
-            else                                                                                                  \
-                hipLaunchKernelGGL((adj_kchi_kernel<T, NB, 1, 8>), dim3((unsigned)((p->n_chi + 15) / 16), a->batch), \
-                                   dim3(512), 0, s, (const T *)Y, Sg, p->d_wchi, p->d_chi, p->n_chi, p->rows,     \
+                                   dim3((unsigned)((p->n_chi + 1024 / NB - 1) / (1024 / NB)), a->batch),          \
+                                   dim3(256), 0, s, (const T *)Y, Sg, p->d_wchi, p->d_chi, p->n_chi, p->rows,     \
                                    p->rows_pad, x.nbins, dK_chi);                                                 \
+            else                                                                                                  \
+                hipLaunchKernelGGL((adj_kchi_kernel<T, NB, 1, 8>),                                                \
+                                   dim3((unsigned)((p->n_chi + 15) / 16), a->batch), dim3(512), 0, s,             \
+                                   (const T *)Y, Sg, p->d_wchi, p->d_chi, p->n_chi, p->rows, p->rows_pad,         \
+                                   x.nbins, dK_chi);                                                              \
         }                                                                                                         \
         const dim3 gw = chi_cosmology_grid(p->n_chi, a->batch);                                                   \
         if constexpr (std::is_same<T, float>::value) {                                                           \
@@ -4282,9 +4284,9 @@ blast_status backward(blast_plan *p, const blast_cl_args *a, const double *dC, v
                                    (const double *)w, a->K_chi2, p->d_wR, a->batch, p->NP, p->n_R, p->n_chi,      \
                                    p->rows, p->rows_pad, x.nbins, (double *)dw, dK_chi2);                         \
             else                                                                                                  \
-            hipLaunchKernelGGL((adj_w_kernel<T, NB>), gw, dim3(256), shw, s, (const T *)dY, (const T *)w,       \
-                               a->K_chi2, p->d_wR, a->batch, p->NP, p->n_R, p->n_chi, p->rows, p->rows_pad, x.nbins, \
-                               (T *)dw, dK_chi2);                                                               \
+                hipLaunchKernelGGL((adj_w_kernel<NB>), gw, dim3(256), shw, s, (const double *)dY, (const double *)w, \
+                                   a->K_chi2, p->d_wR, a->batch, p->NP, p->n_R, p->n_chi, p->rows, p->rows_pad,   \
+                                   x.nbins, (double *)dw, dK_chi2);                                               \
         }                                                                                                         \
     } while (0)
     if (f64 && x.nbp == 16) BLAST_ADJ(double, 16);
