@@ -3894,16 +3894,17 @@ void stage_quad_c(blast_plan *p, const blast_cl_args *a, const Ctx &x, const voi
     const int nc4 = (p->n_chi + 3) & ~3;
     const size_t sh2 = ((size_t)x.nbp * nc4 + 4 * (size_t)x.nbp * x.nbp) * sizeof(double);
     const bool f64 = x.prec == BLAST_FP64;
-    // Work-groups of 4 rows (one per wave) where 16-row ones would leave the chip idle: up to 640 of those, or 1024
-    // on FP64 from 96 chi nodes on.  Measured on 24 to 256 chi nodes, 20 to 96 multipoles, 1 to 100 cosmologies:
-    // 1.1 to 3.2 times the 16-row form's speed up to 600 16-row work-groups; at 768 to 1200 0.82 to 1.07 on FP32,
-    // 0.8 to 1.0 on FP64 of 24 and 64 nodes, 1.0 to 1.22 on more.  Where the table leaves one work-group per CU
-    // (17 bins and more from 190 nodes on) each round of work-groups counts, a table making for a third of a row
-    // (200 nodes, 20 bins, FP32: 204 16-row work-groups 52 us against 61, 162 51 against 47, 306 95 against 74).
+    // Work-groups of 4 rows (one per wave) where 16-row ones would leave the chip idle: up to 2560 of 4 rows, or
+    // 4096 on FP64 from 96 chi nodes on.  Measured on 24 to 256 chi nodes, 20 to 96 multipoles, 1 to 100 cosmologies:
+    // 1.1 to 3.2 times the 16-row form's speed up to 2300 (49 nodes, 34 multipoles, 73 cosmologies: 17 us against
+    // 25); at 3072 to 4800 0.82 to 1.07 on FP32, 0.8 to 1.0 on FP64 of 24 and 64 nodes, 1.0 to 1.22 on more.
+    // Where the table leaves one work-group per CU (17 bins and more from 190 nodes on) each round of work-groups
+    // counts, a table making for a third of a row (200 nodes, 20 bins, FP32, 64 multipoles: 17 cosmologies 61 us
+    // against 52, 9 34 against 51, 31 89 against 97).
     const long w16 = (long)p->nt * nblk * a->batch, w4 = (long)p->nt * ((x.sel.n_out + 3) / 4) * a->batch;
     const bool few = sy.nsplit > 1 ||
-                     (sh2 > 80 * 1024 ? w16 < 640 && 13 * ((w16 + 255) / 256) > 4 * ((w4 + 255) / 256)
-                                      : w16 < (f64 && p->n_chi >= 96 ? 1024 : 640));
+                     (sh2 > 80 * 1024 ? w4 < 2560 && 13 * ((w16 + 255) / 256) > 4 * ((w4 + 255) / 256)
+                                      : w4 < (f64 && p->n_chi >= 96 ? 4096 : 2560));
     auto by_rows = [&](auto ytag, auto nbt) {
         using YT = typename decltype(ytag)::type;
         constexpr int NBT = decltype(nbt)::value;
