@@ -389,9 +389,11 @@ blast_status blast_server_destroy(blast_server *srv);
 /* While enabled, blast_cl_forward records HIP events on the call's stream around
  * four intervals: 0 projection, 1 contraction, 2 R-quadrature, 3 chi-quadrature and
  * pair assembly.  Where the contraction and the R-quadrature run fused (the
- * mixed-precision paths without w_save, FP64 and FP32 below 32 cosmologies, FP64 from
- * there on with at most 16 bins), interval 1 holds the R-quadrature weight table, if the
- * call makes one, and interval 2 the fused kernel.  The events cost a few microseconds per call. */
+ * mixed-precision paths without w_save; FP64 with at most 16 bins from 32 cosmologies
+ * on; most FP64 and FP32 calls below that, and on small grids larger ones too, which
+ * stream the basis), interval 1 holds the R-quadrature weight table, if the call makes
+ * one (streaming calls do not), and interval 2 the fused kernel.  The events cost a few
+ * microseconds per call. */
 blast_status blast_plan_profile(blast_plan *plan, int32_t enable);
 
 /* ------------------------------------------------------------------------ */

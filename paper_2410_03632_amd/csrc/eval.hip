@@ -3400,10 +3400,10 @@ struct Layout {
 // cosmologies per work-group of the adjoint's transposed contraction (their dw rows sit in LDS)
 constexpr int kAdjBT = 32;
 
-// Below this batch FP64 and FP32 stream the basis (stream.hip): there the basis is the traffic, and the
-// fused kernels, which keep one work-group per CU busy with a barrier per b, read it more slowly; from
-// here on two 16-cosmology tiles and more share every basis tile, and the fused kernels' LDS tiles pay.
-// The BF16 paths run unfused below it.
+// Below this batch FP64 and FP32 stream the basis (stream.hip; streams() has the exceptions): there the basis is
+// the traffic, and the fused kernels, which keep one work-group per CU busy with a barrier per b, read it more
+// slowly; from here on two 16-cosmology tiles and more share every basis tile, and the fused kernels' LDS tiles
+// pay, except on small grids.  The BF16 paths run unfused below it.
 constexpr int kFusedMinBatch = 32;
 
 // bins computed by the fused kernel (multiple of 4), 0 when it does not apply

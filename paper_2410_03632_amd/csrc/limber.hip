@@ -57,7 +57,7 @@ __device__ inline void pair_decode(int p, int ng, int ns, uint32_t types, int &t
 // serves both and every multipole of the wave.  Work-group = (16 output multipoles, cosmology),
 // 4 waves of 4 multipoles; the chi nodes go by in chunks of 64 staged in LDS (the stencil of A'
 // is summed while staging: 5 multiply-adds, where a separate pass wrote and re-read a (K, A) table).
-// At full 3x2pt (10 + 5 bins, 96 multipoles, 256 nodes), batch 256: 86 us, of which the 1.6e6 MFMAs
+// At full 3x2pt (10 + 5 bins, 96 multipoles, 256 nodes), batch 256: 86 us a call, of which the 1.6e6 MFMAs
 // of 64 cycles take 41 and the 132 MB of inputs and outputs would take 28; the form with one
 // thread per pair took 452 us plus 15 for its table.  LDS and registers are held to 26 KB and 80
 // so that all six work-groups a CU gets there are resident (four resident: 125 us with the
