@@ -3926,6 +3926,18 @@ void stage_quad_c(blast_plan *p, const blast_cl_args *a, const Ctx &x, const voi
     else by_bins(TypeTag<float>());
 }
 
+// the 16-row tiles that hold a requested multipole of a requested type
+RowTiles row_tiles(const blast_plan *p, const blast_cl_args *a, const Ctx &x, bool all) {
+    RowTiles r{};
+    bool need[3 * kMaxEll / 16] = {};
+    for (int sl = 0; sl < p->nt; ++sl)
+        if (p->tslot_type[sl] & a->types)
+            for (int i = 0; i < x.sel.n_out; ++i) need[(sl * p->n_ell + x.sel.idx[i]) / 16] = true;
+    for (int t = 0; t < p->rows_pad / 16; ++t)
+        if (all || need[t]) r.add(t);
+    return r;
+}
+
 // How a plan's FP64 streaming calls share out the R nodes: ns ranges summed apart, waves per row tile
 struct RSplit {
     int ns, waves;
@@ -3963,7 +3975,9 @@ RSplit r_split(const blast_plan *p, int prec) {
 // tiles FP32 1.1 to 1.3, FP64 0.95 to 1.23 (full 3x2pt 0.92 to 0.96 while less than a quarter of the second tile
 // is used, from there on 0.99 to 1.13), at three FP32 0.92 to 1.06 up to half of the third, then 1.01 to 1.2,
 // FP64 0.81 to 1.05, at four FP32 0.90 to 1.04, FP64 0.75 to 0.93.  FP64 plans that split the R sums stream in any
-// case, for one order of the sums (40 x 29 points, 12 row tiles: 0.95 to 1.07 at three and four tiles).
+// case, for one order of the sums (40 x 29 points, 12 row tiles: 0.95 to 1.07 at three and four tiles), and so do
+// calls that want at most 7 of 8 row tiles (3 of 4 on FP64 from four tiles on), which w's route computes all
+// (full 3x2pt, 15 of 18: FP64, 17 cosmologies, 2013 us against 2336; 20 bins, 24 cosmologies, 2632 against 2952).
 //
 // From there on where the fused kernels (which then take the call otherwise, and whose FP32 sums the streaming
 // kernel repeats bit for bit) have too few work-groups for the chip.  Counted in waves, on grids from 24 x 16 to
@@ -3972,32 +3986,21 @@ RSplit r_split(const blast_plan *p, int prec) {
 // on the larger points 1.1 at 2400, 0.94 at 3840; FP64, whose fused kernel reuses a basis tile for 64 cosmologies
 // where this one reuses it for 16, 1.26 to 1.8 times up to 512 waves and 0.98-1.12 at 768 waves of four row tiles.
 // One row tile leaves three of four waves idle (0.6-1.06).
-bool streams(const blast_plan *p, const Ctx &x, int batch) {
+bool streams(const blast_plan *p, const Ctx &x, int batch, int wanted) {
     const bool f64 = x.prec == BLAST_FP64;
     if (!f64 && x.prec != BLAST_FP32) return false;
     const int RT = p->rows_pad / 16, BT = stream_tile(batch, x.nbins), tiles = (batch + BT - 1) / BT;
     const bool large = RT > 8 && p->nc_pad > 64;  // basis points
     if (batch < kFusedMinBatch) {
         const RSplit r = r_split(p, x.prec);
-        if (tiles == 1 || !large || r.ns > 1 || r.waves > 1) return true;
+        const bool skips = f64 && tiles >= 4 ? 4 * wanted <= 3 * RT : 8 * wanted <= 7 * RT;
+        if (tiles == 1 || !large || r.ns > 1 || r.waves > 1 || skips) return true;
         if (tiles == 2) return !f64 || (size_t)p->rows_pad * p->nc_pad * 8 <= 256 * 1024 || batch >= BT + BT / 4;
         return tiles == 3 && !f64 && batch > 2 * BT + BT / 2;
     }
     if (x.nbins > (f64 ? 16 : 20)) return false;
     const long waves = (long)p->n_chi * ((RT + 3) / 4 * 4) * tiles;
     return RT > 1 && waves <= (f64 ? 512 : BT == 16 ? 2048 : large ? 3072 : 4096);
-}
-
-// the 16-row tiles that hold a requested multipole of a requested type
-RowTiles row_tiles(const blast_plan *p, const blast_cl_args *a, const Ctx &x, bool all) {
-    RowTiles r{};
-    bool need[3 * kMaxEll / 16] = {};
-    for (int sl = 0; sl < p->nt; ++sl)
-        if (p->tslot_type[sl] & a->types)
-            for (int i = 0; i < x.sel.n_out; ++i) need[(sl * p->n_ell + x.sel.idx[i]) / 16] = true;
-    for (int t = 0; t < p->rows_pad / 16; ++t)
-        if (all || need[t]) r.add(t);
-    return r;
 }
 
 // Device memory a call uses in place of plan-owned or caller scratch (the no-alloc entry point)
@@ -4057,7 +4060,8 @@ blast_status forward_impl(blast_plan *p, const blast_cl_args *a, hipStream_t s, 
     void *w = need_w ? (void *)(ws + L.w) : a->w_save;
     void *Y = a->y_save ? a->y_save : (void *)(ws + L.y);
     const bool keep_fused = !need_w && fused_keeps_w(x.prec, x.nbins, a->batch);
-    const bool stream = streams(p, x, a->batch);
+    const RowTiles wanted = row_tiles(p, a, x, a->w_save || a->y_save);
+    const bool stream = streams(p, x, a->batch, wanted.n);
     const int fnb = !stream && (need_w || keep_fused) ? fused_nb(x.prec, x.nbins, a->batch) : 0;
     const bool f64f = !stream && need_w && x.prec == BLAST_FP64 && fused_f64(x.nbins, a->batch);
     YShape sy{1, 0};
@@ -4091,7 +4095,7 @@ blast_status forward_impl(blast_plan *p, const blast_cl_args *a, hipStream_t s, 
         k.K_chi2 = a->K_chi2;
         k.batch = a->batch;
         k.nbins = x.nbins;
-        k.tiles = row_tiles(p, a, x, a->w_save || a->y_save);
+        k.tiles = wanted;
         const RSplit r = r_split(p, x.prec);
         k.nsplit = r.ns;
         k.node_waves = r.waves;

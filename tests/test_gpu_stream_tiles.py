@@ -32,3 +32,8 @@ def test_as_single_calls(n_ell, n_chi, n_R, n_cheb, n_g, n_s):
                                            n_g, n_s, precision=prec) for i in range(b)])
             for n in (8, 9, 10, 16, 17, 19, 20, 21, 24, 25, 31):
                 assert torch.equal(run(n), want[:n]), (prec, n)
+            some = np.arange(n_ell // 3, dtype=np.int32)  # few enough row tiles to stream in any case
+            for n in (17, 31):
+                got = plan.forward(P[:n].to(dt).contiguous(), K[:n].contiguous(), K2[:n].contiguous(), n_g, n_s,
+                                   precision=prec, ell_idx=some)
+                assert torch.equal(got, want[:n, :, :n_ell // 3]), (prec, n)
