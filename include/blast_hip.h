@@ -315,8 +315,9 @@ blast_status blast_cl_backward(blast_plan *plan, const blast_cl_args *args, cons
  *    it touches nearly every tile whatever its count; the requested ones are picked out;
  *  - each request's result depends only on its own inputs (per-cosmology arithmetic never
  *    mixes batch entries and a bucket only adds bins whose kernels are zero), so it is the
- *    same alone and in any mix: bitwise in launches of fewer than 32 requests, and to the
- *    path's rounding in larger ones, whose kernels add up in another order.  The plan's memory
+ *    same alone and in any mix: bitwise on FP64 and FP32 in launches of fewer than 32 requests,
+ *    and to the path's rounding in larger ones and, on FP16X3, in launches of more than 16 bins,
+ *    whose kernels add up in another order.  The plan's memory
  *    (the basis) is fixed by its grids; the budget is the server's. */
 
 typedef struct blast_server blast_server;
